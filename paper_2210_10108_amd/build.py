@@ -20,6 +20,9 @@ SOURCES = ["api.hip", "march.hip", "encode.hip", "mlp.hip", "composite.hip", "po
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # the encoding claims its next work item before it needs it: without this the
+         # compiler broadcasts the atomic's result, and waits for it, at once
+         "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
          "-fhip-fp32-correctly-rounded-divide-sqrt", "-fno-gpu-rdc", "-ffp-contract=on",
          "-Wall", "-Wno-unused-function", "-Wno-unused-variable", "-Wno-unknown-pragmas",
          "-I", os.path.join(HERE, "..", "include")]

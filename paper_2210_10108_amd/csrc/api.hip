@@ -79,7 +79,6 @@ struct pnerf_field {
   int64_t occ_words = 0;
   // workspace: per-ray arrays of one counted batch, per-sample arrays of one chunk
   void* d_rays = nullptr;
-  size_t rays_bytes = 0;
   int rays_cap = 0, rays_hyp = 0;
   void* d_samp[2] = {nullptr, nullptr};  // two sample buffers (pipelined chunks alternate)
   size_t samp_bytes = 0;
@@ -242,6 +241,33 @@ U_t build_bwd_units(const Weights& W, int lpg) {
   return U;
 }
 
+// The encoding's work queues: hashed levels first, so that the first queue of
+// every XCD (queue x of XCD x) holds hashed tables, then the dense ones.
+// Consecutive levels of a kind share a queue, and with it each sample's
+// position, while their tables together fit one XCD's L2 (kGroupBytes).
+void group_levels(DevField& d) {
+  const int64_t entry = d.f16 ? 4 : 8;
+  int n = 0, nq = 0;
+  for (int kind = 0; kind < 2; ++kind) {  // 0: hashed, 1: dense
+    int64_t bytes = 0;
+    bool open = false;
+    for (int l = 0; l < d.L; ++l) {
+      if ((int)d.dense[l] != kind) continue;
+      const int64_t v = kind ? (int64_t)d.n1[l] * d.n1[l] * d.n1[l] : (int64_t)d.T;
+      if (!open || bytes + v * entry > kGroupBytes) {
+        d.q_first[nq++] = n;
+        bytes = 0;
+        open = true;
+      }
+      bytes += v * entry;
+      d.q_level[n++] = l;
+    }
+    if (kind == 0) d.n_hashed_queue = nq;
+  }
+  d.n_queue = nq;
+  for (; nq <= kMaxLevels; ++nq) d.q_first[nq] = n;
+}
+
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Carver {
@@ -258,7 +284,8 @@ struct Carver {
 // Per-ray arrays for n_rays rays (one counted batch).  `offc` receives the
 // sample chunks' own exclusive offsets.
 struct RayWs {
-  float *rdx, *rdy, *rdz, *rtn, *rtf, *rdelta, *rex, *rey, *rez, *rsh;
+  float4* rrec;
+  float *rtn, *rtf, *rdelta, *rsh;
   int32_t *count, *off, *blocksum, *hyp_total;
   int32_t* offc[2];             // per sample buffer: the chunk's own offsets,
   float *ray_loss[2], *partial[2];  // per-ray losses and reduction partials
@@ -270,15 +297,10 @@ size_t carve_rays(int n_rays, int n_hyp, RayWs* r, char* base) {
   const size_t R = (size_t)n_rays;
   RayWs tmp{};
   RayWs& x = r ? *r : tmp;
-  x.rdx = c.take<float>(R);
-  x.rdy = c.take<float>(R);
-  x.rdz = c.take<float>(R);
+  x.rrec = c.take<float4>(R * 3);
   x.rtn = c.take<float>(R);
   x.rtf = c.take<float>(R);
   x.rdelta = c.take<float>(R);
-  x.rex = c.take<float>(R);
-  x.rey = c.take<float>(R);
-  x.rez = c.take<float>(R);
   x.rsh = c.take<float>(R * 16);
   x.count = c.take<int32_t>(R);
   x.off = c.take<int32_t>(R + 1);
@@ -291,6 +313,15 @@ size_t carve_rays(int n_rays, int n_hyp, RayWs* r, char* base) {
     x.ray_terms[q] = c.take<float>(R * 7);
   }
   return c.off;
+}
+
+// What the workspace budget sets aside for the rays: fixed sizes per ray and
+// hypothesis, so that a budget cuts a batch into the same chunks whichever
+// per-ray arrays the kernels keep (carve_rays takes 24 bytes a ray more).
+int64_t budget_rays(int64_t R, int64_t n_hyp) {
+  const auto words = [](int64_t n) { return (int64_t)align_up((size_t)n * 4); };
+  return 11 * words(R) + words(16 * R) + words(R + 1) + words((R + 255) / 256) +
+         2 * (words(R + 1) + words(R) + words(n_hyp * kReduceParts * 7) + words(7 * R));
 }
 
 // Per-sample arrays for cap samples (one chunk); cap is a multiple of kTile.
@@ -318,9 +349,8 @@ DevWork counted_work(pnerf_field* F) {
   RayWs r{};
   carve_rays(F->rays_cap, F->rays_hyp, &r, (char*)F->d_rays);
   DevWork w{};
-  w.rdx = r.rdx; w.rdy = r.rdy; w.rdz = r.rdz;
+  w.rrec = r.rrec;
   w.rtn = r.rtn; w.rtf = r.rtf; w.rdelta = r.rdelta;
-  w.rex = r.rex; w.rey = r.rey; w.rez = r.rez;
   w.rsh = r.rsh;
   w.count = r.count;
   w.off = r.off;
@@ -335,9 +365,8 @@ DevWork chunk_work(pnerf_field* F, int ray_base, int chunk_id, int slot) {
   carve_rays(F->rays_cap, F->rays_hyp, &r, (char*)F->d_rays);
   DevWork w{};
   carve_samples(F->dev, F->samp_cap, &w, (char*)F->d_samp[slot]);
-  w.rdx = r.rdx + ray_base; w.rdy = r.rdy + ray_base; w.rdz = r.rdz + ray_base;
+  w.rrec = r.rrec + (size_t)3 * ray_base;
   w.rtn = r.rtn + ray_base; w.rtf = r.rtf + ray_base; w.rdelta = r.rdelta + ray_base;
-  w.rex = r.rex + ray_base; w.rey = r.rey + ray_base; w.rez = r.rez + ray_base;
   w.rsh = r.rsh + (size_t)16 * ray_base;
   w.count = r.count + ray_base;
   w.off = r.offc[slot];
@@ -383,7 +412,6 @@ pnerf_status ensure_rays(pnerf_field* F, int n_rays, int n_hyp, hipStream_t s, b
     hipError_t e = hipMalloc(&F->d_rays, bytes);
     if (e != hipSuccess)
       return fail(PNERF_ERR_OUT_OF_MEMORY, "ray workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
-    F->rays_bytes = bytes;
     F->rays_cap = n_rays;
     F->rays_hyp = n_hyp;
   }
@@ -570,7 +598,7 @@ pnerf_status run(pnerf_field* F, Mode mode, int32_t K, const float* poses, int32
   if (st != PNERF_OK) return st;
   const int64_t per_sample = bytes_per_sample(F->dev);  // per buffer
   const int64_t limit = std::min<int64_t>(
-      std::max<int64_t>((F->budget - (int64_t)F->rays_bytes) / per_sample, kTile),
+      std::max<int64_t>((F->budget - budget_rays(F->rays_cap, F->rays_hyp)) / per_sample, kTile),
       ((int64_t)1 << 31) - 4 * kTile);
   // loss gradient: several chunks, encoding of one overlapping the networks of
   // the previous, on two internal streams with a sample buffer each
@@ -664,7 +692,9 @@ pnerf_status run(pnerf_field* F, Mode mode, int32_t K, const float* poses, int32
           HIP_TRY(launch_copy_samples(w.t, j_tmp, t_out + grand + base, j_out + grand + base,
                                       sums[c], s));
       } else if (mode == kRender) {
-        HIP_TRY(timed(F, "encode_render", s, [&] { return launch_encode(F->dev, b, w, F->enc_blocks, 0, s); }));
+        HIP_TRY(timed(F, "encode_render", s, [&] {
+          return launch_encode(F->dev, b, w, sums[c], F->enc_blocks, F->n_cu, 0, s);
+        }));
         HIP_TRY(timed(F, "mlp_fwd_render", s, [&] {
           return launch_mlp_fwd(F->dev, b, w, F->fwd_blocks, 0, s);
         }));
@@ -673,7 +703,9 @@ pnerf_status run(pnerf_field* F, Mode mode, int32_t K, const float* poses, int32
         }));
       } else {
         const int eb = overlap ? F->enc_blocks_overlap : F->enc_blocks;
-        HIP_TRY(timed(F, "encode", se, [&] { return launch_encode(F->dev, b, w, eb, 1, se); }));
+        HIP_TRY(timed(F, "encode", se, [&] {
+          return launch_encode(F->dev, b, w, sums[c] >= 0 ? sums[c] : worst, eb, F->n_cu, 1, se);
+        }));
         if (overlap) {
           HIP_TRY(hipEventRecord(F->ev_enc[slot], se));
           HIP_TRY(hipStreamWaitEvent(sm, F->ev_enc[slot], 0));
@@ -837,16 +869,7 @@ pnerf_status pnerf_create_field(const pnerf_field_params* p, void* stream, pnerf
     d.dense[l] = (p->dense_coarse_levels && n1 * n1 * n1 <= d.T) ? 1u : 0u;
   }
   d.f16 = p->param_dtype == 1;
-  // work queues of the encoding kernel, one per level: hashed levels first, so
-  // that the first queue of every XCD (queue x of XCD x) holds a hashed table
-  {
-    int q = 0;
-    for (int l = 0; l < L; ++l)
-      if (!d.dense[l]) d.q_level[q++] = l;
-    for (int l = 0; l < L; ++l)
-      if (d.dense[l]) d.q_level[q++] = l;
-    for (; q < kMaxLevels; ++q) d.q_level[q] = 0;
-  }
+  group_levels(d);
   d.density_bias = p->density_bias;
   d.bf16_neg1[0] = 0x0000BF80u;  // low half -1, high half 0
   d.bf16_neg1[1] = 0xBF800000u;  // low half 0, high half -1
@@ -855,7 +878,8 @@ pnerf_status pnerf_create_field(const pnerf_field_params* p, void* stream, pnerf
     d.mx[a] = p->aabb_max[a];
     float ext = p->aabb_max[a] - p->aabb_min[a];
     d.inv_ext[a] = 1.0f / ext;
-    d.inv_ext_err[a] = (float)((double)d.inv_ext[a] * (double)ext - 1.0);
+    d.inv64[a] = 1.0 / (double)ext;
+    d.mn64[a] = (double)p->aabb_min[a];
   }
   d.march_mode = p->march_mode;
   d.n_uniform = p->n_uniform;
@@ -962,9 +986,10 @@ pnerf_status pnerf_create_field(const pnerf_field_params* p, void* stream, pnerf
   F->bwd_blocks = F->n_cu * mlp_bwd_blocks_per_cu(d.lpg, d.sh_dir_grad, d.mlp_f16);
   F->ray_blocks = F->n_cu * ray_bwd_blocks_per_cu(d.lpg, d.sh_dir_grad, d.mlp_f16);
   F->backward = p->backward;
-  CF_TRY(hipMalloc(&F->d_queue, sizeof(uint32_t) * kMaxLevels * kQueueStride));
-  F->enc_blocks = encode_blocks(d, F->n_cu, 8);
-  F->enc_blocks_overlap = encode_blocks(d, F->n_cu, 4);  // leave room for the networks
+  CF_TRY(hipMalloc(&F->d_queue, sizeof(uint32_t) * (kMaxLevels + 1) * kQueueStride));
+  const int enc_per_cu = encode_blocks_per_cu(d);
+  F->enc_blocks = F->n_cu * enc_per_cu;
+  F->enc_blocks_overlap = F->n_cu * std::max(1, enc_per_cu / 2);  // leave room for the networks
   F->overlap_chunks = p->overlap_chunks == 0 ? kDefaultOverlapChunks : p->overlap_chunks;
   CF_TRY(hipStreamSynchronize(s));
 #undef CF_TRY

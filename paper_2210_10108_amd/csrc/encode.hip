@@ -5,110 +5,120 @@
 // contracts this Jacobian with d loss / d feature, and nothing is re-gathered
 // or scattered).
 //
-// Work split: one level at a time per work item (see k_encode): every XCD
-// (own 4 MB L2) works on one level table at a time, its home levels first.
+// Work split: one group of levels at a time per work item (see k_encode): every
+// XCD (own 4 MB L2) works on one group's tables at a time, its home groups
+// first.
 //
-// Two adjacent lanes handle one sample: lane side 0 gathers the four vertices
-// at the cell's lower x, side 1 the four at x + 1.  The two x neighbours of a
-// vertex nearly always share a cache line: a dense level stores them side by
-// side, and the spatial hash (x ^ y' ^ z') of x and x + 1 differs only in the
-// bits that the carry of x + 1 flips, the lowest bit for even x.  Each gather
-// instruction so touches about half as many lines as with one lane per sample,
-// and the gather's cost follows the lines, not the instructions.  Each lane
-// blends its half; one lane-pair exchange completes the sums.
+// Hashed levels: two adjacent lanes handle one sample: lane side 0 gathers the
+// four vertices at the cell's lower x, side 1 the four at x + 1.  The two x
+// neighbours of a vertex nearly always share a cache line: the spatial hash
+// (x ^ y' ^ z') of x and x + 1 differs only in the bits that the carry of x + 1
+// flips, the lowest bit for even x.  Each gather instruction so touches about
+// half as many lines as with one lane per sample, and the gather's cost follows
+// the lines: a line that misses the CU's L1 takes 2.25 cycles from L2 at best
+// (measured over 1 to 4 MB), and the L1 keeps only about 64 such misses in
+// flight.  Each lane blends its half; one lane-pair exchange completes the
+// sums.  Dense levels take one lane per sample (dense_item).
+//
+// What bounds it: 4 lines per sample and hashed level at the L1's misses in
+// flight times the L2's latency, then the texture unit (16 cycles for any
+// gather instruction, 32 for a 16-byte load) and the vector work beside it.  On
+// 39.5 M samples (16 levels, 2^19 entries, fp32) the kernel takes 7.9 ms
+// against 8.6 ms with per-lane ray lookups, positions recovered in float and a
+// queue per dense level; with every gather in L1 it took 5.0 ms, without
+// gathers 4.2 ms.
 //
 // Features are stored SoA, row p = (l % 4) * 2 LPG + (l / 4) * 2 + q for
 // feature q of level l (the order in which the MLP kernels feed them to MFMA),
 // row stride = the workspace sample capacity.  The Jacobian d feature /
 // d pos of every level (pos = x N_l: bounded by the table's value
 // differences, zero along clamped components) is stored in fp16 (rounding
-// below 2^-11 of each entry), as one 12-byte record per sample and level (the
-// six values d feature_q / d pos_a at 3 q + a), grouped in blocks of 32
-// samples: block b, lane group g = l % 4, level l / 4 of the group, sample
-// s % 32, at ((4 b + g) LPG 32 + (l / 4) 32 + s % 32) 6 halves.  The MLP
-// backward kernel reads each of its samples' records of a lane group with one
-// 12-byte load per level, and the 32 records of one level and block fill 3
-// whole cache lines, so no line is written from two XCDs.  That kernel applies
-// N_l and 1 / extent in fp32.
+// below 2^-11 of each entry), as one 12-byte record per sample and level: three
+// words, (q, a) = (0, 0) (0, 1), then (1, 0) (1, 1), then (0, 2) (1, 2) of
+// d feature_q / d pos_a, grouped in blocks of 32 samples: block b, lane group
+// g = l % 4, level l / 4 of the group, sample s % 32, at record
+// (4 b + g) LPG 32 + (l / 4) 32 + s % 32.  The MLP backward kernel reads each of
+// its samples' records of a lane group with one 12-byte load per level, and the
+// 32 records of one level and block fill 3 whole cache lines, so no line is
+// written from two XCDs.  That kernel applies N_l and 1 / extent in fp32.
+#include <algorithm>
+
 #include "pnerf_internal.h"
 
 namespace pnerf {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int kJacBlock = 32 * 12;  // bytes of one level's Jacobian records of a 32-sample block
 constexpr uint32_t kPrime1 = 2654435761u, kPrime2 = 805459861u;
 
 struct Pos {
   float x[3];        // normalised, clamped position in [0,1]^3 (decides cells)
   float dx[3];       // exact normalised position minus x (0 where clamped)
-  uint32_t clamped;  // bit a set: component a was clamped
 };
 
-// Error-free transformation of a float sum: a + b = s + return value.
-__device__ __forceinline__ float two_sum_err(float a, float b, float s) {
-  float bb = __fsub_rn(s, a);
-  return __fadd_rn(__fsub_rn(a, __fsub_rn(s, bb)), __fsub_rn(b, bb));
-}
-
 // Sample position p = o + t d and x = (p - min) / extent.  The float chain
-// (separately rounded, never fused) decides cells and clamping; the rounding
-// errors of each step are recovered exactly (TwoSum / FMA) together with the
-// float direction's own error, so that dx carries x's exact value to first
-// order and interpolation weights are accurate to float precision.
-__device__ inline Pos sample_pos(const DevField& f, const DevBatch& b, const DevWork& w, int s) {
+// (separately rounded, never fused) decides cells and clamping; x in double,
+// along the ray's direction in double, gives dx, what float cannot hold of the
+// position, so that interpolation weights are accurate to float precision.
+// (The double chain is 21 instructions for the three axes; recovering every
+// rounding error of the float chain in float took about 50.)
+// clamped: bit a set where component a was clamped.  A sample is clamped only
+// when rounding puts it outside the box (or its pose is not finite), so the
+// clamps run behind a test of the whole wavefront: 0 <= x <= 1 as unsigned
+// bit patterns (negative values, -0 and NaN are all above 1's).
+__device__ __forceinline__ Pos sample_pos(const DevField& f, float t, const RayRecord& r,
+                                          uint32_t& clamped) {
   Pos ps;
-  int ray = w.sray[s];
-  const float* pose = b.poses + 12 * (ray / b.P);
-  const float o[3] = {pose[3], pose[7], pose[11]};
-  const float d[3] = {w.rdx[ray], w.rdy[ray], w.rdz[ray]};
-  const float de[3] = {w.rex[ray], w.rey[ray], w.rez[ray]};
-  const float t = w.t[s];
-  ps.clamped = 0;
+  float o[3], d[3];
+  double D[3];
+  r.origin(o);
+  r.dir(d);
+  r.dir64(D);
+  const double t64 = (double)t;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    float td = __fmul_rn(t, d[a]);
-    float e_td = fmaf(t, d[a], -td) + t * de[a];
-    float p = __fadd_rn(o[a], td);
-    float e_p = two_sum_err(o[a], td, p);
-    float q = __fsub_rn(p, f.mn[a]);
-    float e_q = two_sum_err(p, -f.mn[a], q);
-    float xr = __fmul_rn(q, f.inv_ext[a]);
-    float e_x = fmaf(q, f.inv_ext[a], -xr);
-    float dx = e_x + (e_td + e_p + e_q) * f.inv_ext[a] - xr * f.inv_ext_err[a];
-    if (!(xr >= 0.0f)) {  // below the box (or NaN from a non-finite pose)
-      ps.x[a] = 0.0f;
-      ps.dx[a] = 0.0f;
-      ps.clamped |= 1u << a;
-    } else if (xr > 1.0f) {
-      ps.x[a] = 1.0f;
-      ps.dx[a] = 0.0f;
-      ps.clamped |= 1u << a;
-    } else {
-      ps.x[a] = xr;
-      ps.dx[a] = dx;
+    const float p = __fadd_rn(o[a], __fmul_rn(t, d[a]));
+    ps.x[a] = __fmul_rn(__fsub_rn(p, f.mn[a]), f.inv_ext[a]);
+    const double x64 = (fma(t64, D[a], (double)o[a]) - f.mn64[a]) * f.inv64[a];
+    ps.dx[a] = (float)(x64 - (double)ps.x[a]);
+  }
+  clamped = 0;
+  const uint32_t top = max(max(__float_as_uint(ps.x[0]), __float_as_uint(ps.x[1])),
+                           __float_as_uint(ps.x[2]));
+  if (__any(top > 0x3F800000u)) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      if (!(ps.x[a] >= 0.0f)) {  // below the box (or NaN from a non-finite pose)
+        ps.x[a] = 0.0f;
+        ps.dx[a] = 0.0f;
+        clamped |= 1u << a;
+      } else if (ps.x[a] > 1.0f) {
+        ps.x[a] = 1.0f;
+        ps.dx[a] = 0.0f;
+        clamped |= 1u << a;
+      }
     }
   }
   return ps;
 }
 
-// The position held by lane ODD of each lane pair, in both lanes of the pair
+// The value held by lane ODD of each lane pair, in both lanes of the pair
 // (DPP quad_perm [0,0,2,2] or [1,1,3,3]; all lanes active).
 template <int ODD>
 __device__ __forceinline__ float from_pair_lane(float v) {
   return __int_as_float(
-      __builtin_amdgcn_update_dpp(0, __float_as_int(v), ODD ? 0xF5 : 0xA0, 0xF, 0xF, false));
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), ODD ? 0xF5 : 0xA0, 0xF, 0xF, true));
 }
 
 template <int ODD>
 __device__ __forceinline__ Pos pos_from_pair_lane(const Pos& p) {
-  auto bc = from_pair_lane<ODD>;
   Pos r;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    r.x[a] = bc(p.x[a]);
-    r.dx[a] = bc(p.dx[a]);
+    r.x[a] = from_pair_lane<ODD>(p.x[a]);
+    r.dx[a] = from_pair_lane<ODD>(p.dx[a]);
   }
-  r.clamped = (uint32_t)__float_as_int(bc(__int_as_float((int)p.clamped)));
   return r;
 }
 
@@ -120,11 +130,9 @@ struct Cell {
 };
 
 // The cell comes from the float product x N (as a reference implementation in
-// float decides it); the weights add back that product's rounding error and
-// N dx, the part of the position float cannot hold.
-__device__ __forceinline__ void make_cell(const DevField& f, int l, const float x[3],
-                                          const float dx[3], Cell& c) {
-  const int N = f.res[l];
+// float decides it); the weights are x N - cell, rounded once, plus N dx, the
+// part of the position float cannot hold.
+__device__ __forceinline__ void make_cell(int N, const float x[3], const float dx[3], Cell& c) {
   const float Nf = (float)N;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -132,14 +140,12 @@ __device__ __forceinline__ void make_cell(const DevField& f, int l, const float 
     int ci = (int)pos;
     ci = ci < N - 1 ? ci : N - 1;
     c.i0[a] = (uint32_t)ci;
-    c.w[a] = (__fsub_rn(pos, (float)ci) + fmaf(x[a], Nf, -pos)) + Nf * dx[a];
+    c.w[a] = fmaf(Nf, dx[a], fmaf(x[a], Nf, -(float)ci));
   }
 }
 
-// KIND: 0 the level's kind read from the field, 1 dense, 2 hashed.
-template <int KIND>
 __device__ __forceinline__ uint32_t corner_index(const DevField& f, int l, const Cell& c, int k) {
-  const bool dense = KIND == 0 ? f.dense[l] != 0 : KIND == 1;
+  const bool dense = f.dense[l] != 0;
   const uint32_t n1 = f.n1[l];
   const uint32_t sy = dense ? n1 : kPrime1;
   const uint32_t sz = dense ? n1 * n1 : kPrime2;
@@ -166,10 +172,10 @@ template <bool F16>
 __device__ __forceinline__ float2 level_feature(const DevField& f, int l, const float x[3],
                                                 const float dx[3], float* jac) {
   Cell c;
-  make_cell(f, l, x, dx, c);
+  make_cell(f.res[l], x, dx, c);
   float2 v[8];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) v[k] = vertex<F16>(f, corner_index<0>(f, l, c, k));
+  for (int k = 0; k < 8; ++k) v[k] = vertex<F16>(f, corner_index(f, l, c, k));
   const float wx = c.w[0], wy = c.w[1], wz = c.w[2];
   const float ux = 1.0f - wx, uy = 1.0f - wy, uz = 1.0f - wz;
   float2 r;
@@ -194,186 +200,442 @@ __device__ __forceinline__ float2 level_feature(const DevField& f, int l, const 
   return r;
 }
 
-// One lane's half of level l: the four corners with x offset `side`, blended
-// with that side's x weight.  p = (feature_0, feature_1, then when GRAD the
-// half of d feature_q / d pos_a at 2 + 3 q + a).  The halves of the two lanes
-// of a pair add up to the whole cell's values.  KIND: see corner_index.
-template <bool F16, bool GRAD, int KIND>
-__device__ __forceinline__ void half_cell(const DevField& f, int l, const float x[3],
-                                          const float dx[3], int side, float p[8]) {
-  Cell c;
-  make_cell(f, l, x, dx, c);
-  float2 v[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) v[j] = vertex<F16>(f, corner_index<KIND>(f, l, c, 2 * j + side));
-  const float wx = c.w[0], wy = c.w[1], wz = c.w[2];
-  const float ux = 1.0f - wx, uy = 1.0f - wy, uz = 1.0f - wz;
-  const float sx = side ? wx : ux;       // this side's x weight
-  const float sgn = side ? 1.0f : -1.0f; // its derivative along x
+// Table entry at byte offset `off` from a level's (uniform) base: an
+// instruction with a scalar base and a 32-bit lane offset (T <= 2^24 entries).
+template <bool F16>
+__device__ __forceinline__ float2 entry(const char* base, uint32_t off) {
+  if (F16) return __half22float2(*reinterpret_cast<const __half2*>(base + off));
+  return *reinterpret_cast<const float2*>(base + off);
+}
+
+// A level as the gather sees it, uniform over a work item (read once per item,
+// not once per sample).
+struct Level {
+  const char* table;
+  int res;
+  uint32_t mask;  // table entries - 1
+};
+
+// The four corners of a lane's half of a cell: byte offsets in the level's table
+// (bit 0 of the index: y + 1, bit 1: z + 1).
+//
+// Dense: one 24-bit multiply-add per axis (n1^2 < 2^16), and the four corners
+// are four scalar bases with one lane offset.  Hashed: bits below T <= 2^24 of
+// y p1 and z p2 follow from the factors' low 24 bits (y, z <= 2^20), so 24-bit
+// multiplies do; the second row is the first plus the prime, and everything is
+// kept shifted by the entry size.
+template <bool F16>
+__device__ __forceinline__ uint32_t dense_offset(const Level& lv, const Cell& c, int side) {
+  const uint32_t n1 = lv.res + 1;
+  return (__umul24(__umul24(c.i0[2], n1) + c.i0[1], n1) + c.i0[0] + side) << (F16 ? 2 : 3);
+}
+
+template <bool F16>
+__device__ __forceinline__ void hashed_offsets(const Level& lv, const Cell& c, int side,
+                                               uint32_t off[4]) {
+  constexpr int kShift = F16 ? 2 : 3;  // log2 of an entry's bytes
+  const uint32_t mask = lv.mask << kShift;
+  const uint32_t y0 = __umul24(c.i0[1], kPrime1 & 0xFFFFFFu) << kShift;
+  const uint32_t z0 = __umul24(c.i0[2], kPrime2 & 0xFFFFFFu) << kShift;
+  const uint32_t y1 = y0 + (kPrime1 << kShift), z1 = z0 + (kPrime2 << kShift);
+  const uint32_t x0 = (c.i0[0] + side) << kShift;
+  const uint32_t a0 = x0 ^ y0, a1 = x0 ^ y1;
+  off[0] = (a0 ^ z0) & mask;
+  off[1] = (a1 ^ z0) & mask;
+  off[2] = (a0 ^ z1) & mask;
+  off[3] = (a1 ^ z1) & mask;
+}
+
+// Blend of the four corners over y and z: v[0..1] the two features, and when
+// GRAD v[2 + q] and v[4 + q] their derivatives along y and z.
+template <bool GRAD>
+__device__ __forceinline__ void blend_yz(const float2 e[4], const float wt[3], float v[6]) {
+  const float wy = wt[1], wz = wt[2];
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     float t[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) t[j] = q ? v[j].y : v[j].x;
-    // corners j: bit 0 = y + 1, bit 1 = z + 1
-    const float ty0 = uz * t[0] + wz * t[2], ty1 = uz * t[1] + wz * t[3];
-    p[q] = sx * (uy * ty0 + wy * ty1);
+    for (int j = 0; j < 4; ++j) t[j] = q ? e[j].y : e[j].x;
+    const float dz0 = t[2] - t[0], dz1 = t[3] - t[1];
+    const float a0 = fmaf(wz, dz0, t[0]), a1 = fmaf(wz, dz1, t[1]);
+    const float dy = a1 - a0;
+    v[q] = fmaf(wy, dy, a0);
     if (GRAD) {
-      p[2 + 3 * q + 0] = sgn * (uy * ty0 + wy * ty1);
-      p[2 + 3 * q + 1] = sx * (ty1 - ty0);
-      p[2 + 3 * q + 2] = sx * (uy * (t[2] - t[0]) + wy * (t[3] - t[1]));
+      v[2 + q] = dy;
+      v[4 + q] = fmaf(wy, dz1 - dz0, dz0);
     }
   }
 }
 
-__device__ __forceinline__ int feat_row(const DevField& f, int l, int q) {
-  return (l & 3) * 2 * f.lpg + (l >> 2) * 2 + q;
+// Where a level's outputs go, from a uniform sample index `first` (a multiple of
+// 32): the entries of feature rows q = 0, 1 and of the Jacobian records.  A lane
+// adds a 32-bit byte offset (record_offset for the records), so that the stores
+// take a scalar base each and no 64-bit addresses per lane.
+typedef __attribute__((address_space(1))) char* global_ptr;
+struct LevelOut {
+  global_ptr feat[2], jac;
+};
+
+__device__ __forceinline__ LevelOut level_out(const DevField& f, const DevWork& w, int l,
+                                              int first) {
+  const int64_t row = (l & 3) * 2 * f.lpg + (l >> 2) * 2;
+  LevelOut o;
+  o.feat[0] = (global_ptr)(w.feat + row * w.cap + first);
+  o.feat[1] = (global_ptr)(w.feat + (row + 1) * w.cap + first);
+  o.jac = (global_ptr)w.jac +
+          ((int64_t)(first >> 5) * 4 * f.lpg + (l & 3) * f.lpg + (l >> 2)) * kJacBlock;
+  // opaque, or the compiler adds the lane's offset to the arrays' bases first
+  // and carries 64-bit lane addresses through the whole kernel
+  asm("" : "+s"(o.feat[0]), "+s"(o.feat[1]), "+s"(o.jac));
+  return o;
 }
 
-// Index (in 32-bit words) of the Jacobian record of level l and sample s: six
-// fp16 values d feature_q / d pos_a at 3 q + a, three words.
-__device__ __forceinline__ int64_t jac_record(const DevField& f, int l, int64_t s) {
-  const int kg = 6 * f.lpg * 32;  // halves of one lane group's share of a 32-sample block
-  return (((s >> 5) * 4 + (l & 3)) * (int64_t)kg + ((l >> 2) * 32 + (s & 31)) * 6) / 2;
+// Byte offset of sample first + i's record from LevelOut::jac.
+__device__ __forceinline__ uint32_t record_offset(const DevField& f, int i) {
+  return (uint32_t)((i >> 5) * 4 * f.lpg * kJacBlock + (i & 31) * 12);
 }
 
+template <class T>
+__device__ __forceinline__ void stream_out(global_ptr base, uint32_t off, T v) {
+  __builtin_nontemporal_store(v, (__attribute__((address_space(1))) T*)(base + off));
+}
+
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+
+// Two floats as fp16, rounded to nearest (one packed convert).
 __device__ __forceinline__ uint32_t pack_half2(float lo, float hi) {
-  return (uint32_t)__half_as_ushort(__float2half_rn(lo)) |
-         ((uint32_t)__half_as_ushort(__float2half_rn(hi)) << 16);
+  const half2_t h = {(_Float16)lo, (_Float16)hi};
+  return __builtin_bit_cast(uint32_t, h);
 }
 
 // ------------------------------------------------------------------ forward
-// Work items: kItem consecutive samples of one level, taken from that level's
-// queue (a counter of the items handed out) by one atomic per block.  Queue q
-// serves level q_level[q], hashed levels first.  Workgroups are dispatched
+// Work items: a run of consecutive samples on a group of levels, taken from
+// that group's queue (a counter of the items handed out) by one atomic per
+// block.  Hashed groups come first, dense ones last.  Workgroups are dispatched
 // round-robin over the XCDs, so block b runs on XCD b % 8: it starts on its
-// home queues x, x + 8, ... (x = b % 8), one level at a time, so that each
-// XCD's L2 holds one level table at a time, and once those are drained it
-// takes what is left on every other queue in turn.  No XCD idles while
-// another still has work, and blocks that find no free slot at launch and
-// start late only take what is left.  The next item is claimed before the
-// current one is gathered, hiding the atomic's latency.
+// home queues x, x + 8, ... (x = b % 8), one group at a time, so that each
+// XCD's L2 holds one group's tables at a time (a group's tables fit the L2:
+// group_levels in api.hip), and once those are drained it takes what is left
+// on the other queues in turn.  No XCD idles while another still has work, and
+// blocks that find no free slot at launch and start late only take what is
+// left.  The next item is claimed before the current one is gathered, hiding
+// the atomic's latency.
 constexpr int kXcds = 8;
-constexpr int kPerPair = 4;                      // samples per lane pair and item
-constexpr int kItem = kBlock / 2 * kPerPair;     // samples per work item
-static_assert((kBlock / 2) % 32 == 0, "a lane-pair step must span whole 32-sample Jacobian blocks");
+constexpr int kPerWave = 128;                    // hashed: samples per wavefront and item (4 per lane pair)
+constexpr int kItem = kBlock / 64 * kPerWave;    // hashed: samples per work item
+constexpr int kDenseItem = kBlock;               // dense: samples per work item, one per lane
+constexpr int kWaveRays = 64;                    // ray records a wavefront keeps in LDS
 
 __device__ __forceinline__ uint32_t take_item(uint32_t* queue, int q) {
   return __hip_atomic_fetch_add(queue + q * kQueueStride, 1u, __ATOMIC_RELAXED,
                                 __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A lane pair's share of level l for the sample at ps: lane side q keeps
-// feature q and its Jacobian row, adding the partner's half of those to its
-// own, and hands over its half of the other feature; it stores feature q at fo
-// (the sample's entry of feature row q).  GRAD: lane side 0 also takes the
-// partner's Jacobian row and stores the sample's whole record at jr.  Outputs
-// are streamed out with non-temporal stores so that they do not displace the
-// level tables from L2.
-template <bool F16, bool GRAD, int KIND>
-__device__ __forceinline__ void encode_level(const DevField& f, int l, const Pos& ps, int side,
-                                             float* fo, uint32_t* jr) {
-  float p[8];
-  half_cell<F16, GRAD, KIND>(f, l, ps.x, ps.dx, side, p);
-  const float keep = side ? p[1] : p[0];
-  const float give = side ? p[0] : p[1];
-  __builtin_nontemporal_store(keep + lane_pair_swap(give), fo);
+// The next queue for a block with home queue `home`, in the order home + 8, then
+// home + 1, home + 2, ... round; -1 when every queue in `drained` is.
+__device__ __forceinline__ int next_queue(int home, int n_queue, uint32_t drained) {
+  const uint32_t open = ~drained & ((1u << n_queue) - 1u);
+  if (open == 0) return -1;
+  const uint32_t homes = open & (0x01010101u << (home & 7));  // home, home + 8, ...
+  if (homes) return __ffs(homes) - 1;
+  const uint32_t later = open >> home >> 1 << home << 1;
+  return __ffs(later ? later : open) - 1;
+}
+
+__device__ __forceinline__ uint32_t pair_swap_u(uint32_t x) {
+  return (uint32_t)__float_as_int(lane_pair_swap(__int_as_float((int)x)));
+}
+
+// A lane's part of one sample on one level: feature q (q = lane side) and, when
+// GRAD, its Jacobian row as fp16.  With A the half at x, B the half at x + 1 of
+// a quantity, the blend is A + wx (B - A): the own side's weight times the own
+// half plus the other weight times the half the partner hands over; the
+// derivative along x is B - A.
+struct Part {
+  float feat;
+  uint32_t j01, j2;  // d feature_q / d pos_0 and _1; / d pos_2 in the low half
+};
+
+template <bool GRAD>
+__device__ __forceinline__ Part finish_part(const float2 e[4], const float wt[3], int side) {
+  float v[6];
+  blend_yz<GRAD>(e, wt, v);
+  const float wx = wt[0], ux = 1.0f - wx;
+  const float own = side ? wx : ux, other = side ? ux : wx;
+  const float keep = side ? v[1] : v[0];
+  const float got = lane_pair_swap(side ? v[0] : v[1]);
+  Part r{fmaf(other, got, own * keep), 0, 0};
   if (GRAD) {
-    float v[3], o[3];
+    float j[3];
+    j[0] = side ? keep - got : got - keep;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const float jk = side ? p[5 + a] : p[2 + a];
-      const float jg = side ? p[2 + a] : p[5 + a];
-      v[a] = jk + lane_pair_swap(jg);
-      v[a] = (ps.clamped >> a) & 1u ? 0.0f : v[a];
+    for (int a = 1; a < 3; ++a) {
+      const float jk = side ? v[2 * a + 1] : v[2 * a];
+      const float jg = lane_pair_swap(side ? v[2 * a] : v[2 * a + 1]);
+      j[a] = fmaf(other, jg, own * jk);
     }
+    r.j01 = pack_half2(j[0], j[1]);
+    r.j2 = pack_half2(j[2], 0.0f);
+  }
+  return r;
+}
+
+// The record of this lane's ray, for a wavefront whose samples are in ray order
+// from ray r0 to ray r1: the rays' records are read once each and handed out
+// through LDS, since a record is three 16-byte loads and the texture unit,
+// which every load of the kernel passes, takes 32 cycles for each of a
+// wavefront's 16-byte loads.  A wavefront with more rays than slots (many rays
+// without samples in between) reads one record per lane instead.
+__device__ __forceinline__ RayRecord wave_record(const DevWork& w, float4* lds, int lane, int ray,
+                                                 int r0, int r1) {
+  const bool each = r1 - r0 >= kWaveRays;
+  const int n = each ? 64 : r1 - r0 + 1;
+  for (int i = lane; i < n; i += 64) {
+    const RayRecord r = load_ray(w.rrec, each ? ray : r0 + i);
+    lds[3 * i] = r.a;
+    lds[3 * i + 1] = r.b;
+    lds[3 * i + 2] = r.c;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const RayRecord r = load_ray(lds, each ? lane : ray - r0);
+  __builtin_amdgcn_wave_barrier();
+  return r;
+}
+
+__device__ __forceinline__ Level level_of(const DevField& f, int l) {
+  Level lv;
+  lv.res = f.res[l];
+  lv.mask = f.T - 1u;
+  lv.table = f.f16 ? reinterpret_cast<const char*>(f.table16 + 2 * (size_t)l * f.T)
+                   : reinterpret_cast<const char*>(f.table32 + 2 * (size_t)l * f.T);
+  return lv;
+}
+
+// No derivative along a sample's clamped axes (record order: see finish).
+__device__ __forceinline__ void clear_clamped(uint32_t r[3], uint32_t clamped) {
+  const uint32_t keep = (clamped & 1u ? 0u : 0xFFFFu) | (clamped & 2u ? 0u : 0xFFFF0000u);
+  r[0] &= keep;
+  r[1] &= keep;
+  r[2] = clamped & 4u ? 0u : r[2];
+}
+
+// One wavefront's 128 samples from `first` on hashed levels, as four runs of 32:
+// the pair of lanes 2 i, 2 i + 1 gathers sample i of every run, so that each
+// gather instruction covers consecutive samples and its lanes share lines
+// (the L1 holds only 256 lines, eight such instructions' worth: lines shared
+// between instructions are often evicted in between).  Side q computes the
+// positions of runs 2 k + q, and both lanes take each from the lane that
+// computed it.  Samples past the last one (up to the next multiple of 64, which
+// the buffers hold) repeat it.  Outputs are streamed out with non-temporal
+// stores so that they do not displace the level tables from L2.
+template <bool F16, bool GRAD>
+__device__ __forceinline__ void hashed_item(const DevField& f, const DevWork& w, float4* lds,
+                                            int lane, int first, int S, int q_first, int q_count) {
+  const int side = lane & 1;
+  const int own = 32 * side + (lane >> 1);  // this lane's sample of step k: first + own + 64 k
+  const uint32_t so = own * 4, jo = record_offset(f, own);
+  float t[2];
+  int ray[2];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) o[a] = lane_pair_swap(v[a]);  // side 0: feature 1's row
-    if (side == 0) {
-      __builtin_nontemporal_store(pack_half2(v[0], v[1]), jr);
-      __builtin_nontemporal_store(pack_half2(v[2], o[0]), jr + 1);
-      __builtin_nontemporal_store(pack_half2(o[1], o[2]), jr + 2);
+  for (int k = 0; k < 2; ++k) {
+    const uint32_t i = (uint32_t)min(own + 64 * k, S - 1 - first);
+    ray[k] = (w.sray + first)[i];
+    t[k] = (w.t + first)[i];
+  }
+  Pos mine[2];
+  uint32_t cl[2];  // clamped axes of the samples this lane computed
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    mine[k] = sample_pos(f, t[k], wave_record(w, lds, lane, ray[k],
+                                              __builtin_amdgcn_readfirstlane(ray[k]),
+                                              __builtin_amdgcn_readlane(ray[k], 63)), cl[k]);
+    __builtin_amdgcn_sched_barrier(0);  // one record's registers at a time
+  }
+  const bool any_clamped = __any((cl[0] | cl[1]) != 0);
+  for (int i = 0; i < q_count; ++i) {
+    const int l = f.q_level[q_first + i];
+    const Level lv = level_of(f, l);
+    float wt[2][3];
+    float2 e[2][4];
+    auto gather = [&](int k) {  // runs 2 k and 2 k + 1
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const Pos ps = j ? pos_from_pair_lane<1>(mine[k]) : pos_from_pair_lane<0>(mine[k]);
+        Cell c;
+        make_cell(lv.res, ps.x, ps.dx, c);
+        uint32_t off[4];
+        hashed_offsets<F16>(lv, c, side, off);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) e[j][q] = entry<F16>(lv.table, off[q]);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) wt[j][a] = c.w[a];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    gather(0);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const Part p0 = finish_part<GRAD>(e[0], wt[0], side);
+      const Part p1 = finish_part<GRAD>(e[1], wt[1], side);
+      // side q completes its own sample (run 2 k + q): it hands the partner its
+      // part of the other one.  Record: axes 0 and 1 of feature 0, the same of
+      // feature 1, axis 2 of both
+      float fq[2];
+      uint32_t r[3];
+      {
+        const float kept = side ? p1.feat : p0.feat, got = lane_pair_swap(side ? p0.feat : p1.feat);
+        fq[0] = side ? got : kept;
+        fq[1] = side ? kept : got;
+      }
+      if (GRAD) {
+        const uint32_t k01 = side ? p1.j01 : p0.j01, g01 = pair_swap_u(side ? p0.j01 : p1.j01);
+        const uint32_t k2 = side ? p1.j2 : p0.j2, g2 = pair_swap_u(side ? p0.j2 : p1.j2);
+        r[0] = side ? g01 : k01;
+        r[1] = side ? k01 : g01;
+        r[2] = side ? g2 | (k2 << 16) : k2 | (g2 << 16);
+        if (any_clamped) clear_clamped(r, cl[k]);
+      }
+      if (first + 64 * k < S) {
+        const LevelOut o = level_out(f, w, l, first + 64 * k);
+        stream_out(o.feat[0], so, fq[0]);
+        stream_out(o.feat[1], so, fq[1]);
+        if (GRAD) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) stream_out(o.jac, jo + 4 * a, r[a]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (k == 0) gather(1);
+    }
+  }
+}
+
+// One wavefront's 64 samples from `first` on dense levels, one per lane.
+// Consecutive samples of a ray mostly share a dense level's cells, so a
+// wavefront's gathers touch few lines however the lanes are split, and the
+// vector work sets the time: one lane per sample does the cell and the
+// positions once (about 80 instructions a sample and level against 190 over a
+// lane pair), and the group's levels share the sample's position.
+template <bool F16, bool GRAD>
+__device__ __forceinline__ void dense_item(const DevField& f, const DevWork& w, float4* lds,
+                                           int lane, int first, int S, int q_first, int q_count) {
+  const uint32_t at = (uint32_t)min(lane, S - 1 - first);
+  const int ray = (w.sray + first)[at];
+  const float t = (w.t + first)[at];
+  const uint32_t so = lane * 4, jo = record_offset(f, lane);
+  uint32_t clamped;
+  const Pos ps = sample_pos(f, t, wave_record(w, lds, lane, ray, __builtin_amdgcn_readfirstlane(ray),
+                                              __builtin_amdgcn_readlane(ray, 63)), clamped);
+  const bool any_clamped = __any(clamped != 0);
+  for (int i = 0; i < q_count; ++i) {
+    const int l = f.q_level[q_first + i];
+    const Level lv = level_of(f, l);
+    Cell c;
+    make_cell(lv.res, ps.x, ps.dx, c);
+    const uint32_t off = dense_offset<F16>(lv, c, 0);
+    const uint32_t n1 = lv.res + 1, r1 = n1 << (F16 ? 2 : 3), r2 = n1 * r1;
+    float2 lo[4], hi[4];  // bit 0 of the index: y + 1, bit 1: z + 1
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const char* row = lv.table + (k & 1 ? r1 : 0) + (k & 2 ? r2 : 0);
+      lo[k] = entry<F16>(row, off);
+      hi[k] = entry<F16>(row + (F16 ? 4 : 8), off);
+    }
+    float feat[2], j[2][3];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      float x[4], dx[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float a = q ? lo[k].y : lo[k].x, b = q ? hi[k].y : hi[k].x;
+        dx[k] = b - a;
+        x[k] = fmaf(c.w[0], dx[k], a);
+      }
+      const float dz0 = x[2] - x[0], dz1 = x[3] - x[1];
+      const float y0 = fmaf(c.w[2], dz0, x[0]), y1 = fmaf(c.w[2], dz1, x[1]);
+      const float dy = y1 - y0;
+      feat[q] = fmaf(c.w[1], dy, y0);
+      if (GRAD) {
+        const float ex0 = fmaf(c.w[2], dx[2] - dx[0], dx[0]), ex1 = fmaf(c.w[2], dx[3] - dx[1], dx[1]);
+        j[q][0] = fmaf(c.w[1], ex1 - ex0, ex0);
+        j[q][1] = dy;
+        j[q][2] = fmaf(c.w[1], dz1 - dz0, dz0);
+      }
+    }
+    const LevelOut o = level_out(f, w, l, first);
+    stream_out(o.feat[0], so, feat[0]);
+    stream_out(o.feat[1], so, feat[1]);
+    if (GRAD) {
+      uint32_t r[3] = {pack_half2(j[0][0], j[0][1]), pack_half2(j[1][0], j[1][1]),
+                       pack_half2(j[0][2], j[1][2])};
+      if (any_clamped) clear_clamped(r, clamped);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) stream_out(o.jac, jo + 4 * a, r[a]);
     }
   }
 }
 
 template <bool F16, bool GRAD>
 __global__ __launch_bounds__(kBlock) void k_encode(DevField f, DevBatch b, DevWork w) {
+  __shared__ int s_q[2];
   __shared__ uint32_t s_item[2];
+  __shared__ float4 s_rec[kBlock / 64][3 * kWaveRays];
   const int S = *w.total;
-  const uint32_t n_items = (uint32_t)((S + kItem - 1) / kItem);
-  const int NQ = f.L;
-  const int side = threadIdx.x & 1;
-  const int home = (int)(blockIdx.x % kXcds) < NQ ? (int)(blockIdx.x % kXcds) : (int)(blockIdx.x % NQ);
+  const uint32_t n_hashed = (uint32_t)((S + kItem - 1) / kItem);
+  const uint32_t n_dense = (uint32_t)((S + kDenseItem - 1) / kDenseItem);
+  const int lane = threadIdx.x & 63;
+  // uniform values in scalar registers: they make the output and table bases scalar
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int home = (int)(blockIdx.x % kXcds) % f.n_queue;
+  uint32_t* known = w.queue + kMaxLevels * kQueueStride;  // bits of drained queues
+  uint32_t drained = 0;                                   // thread 0's copy
   int q = home;
-  int visit = 0;  // 0: on the home queues; v > 0: on queue (home + v) % NQ
   int buf = 0;
-  if (threadIdx.x == 0) s_item[buf] = take_item(w.queue, q);
+  if (threadIdx.x == 0) s_item[0] = take_item(w.queue, q);
   __syncthreads();
-  uint32_t item = s_item[buf];
-  // control flow below is uniform over the block: item, q and visit follow
-  // from the same shared words for every thread
+  uint32_t item = __builtin_amdgcn_readfirstlane(s_item[0]);
+  // control flow below is uniform over the block: item and q follow from the
+  // same shared words for every thread
   while (true) {
-    if (item >= n_items) {  // queue q is drained: the next home queue, else the others in turn
-      if (visit == 0 && q + kXcds < NQ) {
-        q += kXcds;
-      } else {
-        if (visit == NQ) break;
-        ++visit;
-        q = (home + visit) % NQ;
-      }
+    const bool hashed = q < f.n_hashed_queue;
+    const uint32_t n_items = hashed ? n_hashed : n_dense;
+    if (item >= n_items) {  // queue q is drained
       buf ^= 1;
-      if (threadIdx.x == 0) s_item[buf] = take_item(w.queue, q);
+      if (threadIdx.x == 0) {
+        // The first block past a queue's end tells the others, who then skip it
+        // (each trip to a counter is a microsecond, and on a small batch they
+        // were most of the kernel).  A stale word costs a trip: every block
+        // also notes the queues it found drained, so it ends after n_queue.
+        drained |= 1u << q;
+        if (item == n_items)
+          __hip_atomic_fetch_or(known, 1u << q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        drained |= __hip_atomic_load(known, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int nq = next_queue(home, f.n_queue, drained);
+        s_q[buf] = nq;
+        if (nq >= 0) s_item[buf] = take_item(w.queue, nq);
+      }
       __syncthreads();
-      item = s_item[buf];
+      q = __builtin_amdgcn_readfirstlane(s_q[buf]);
+      if (q < 0) break;
+      item = __builtin_amdgcn_readfirstlane(s_item[buf]);
       continue;
     }
     uint32_t next = 0;
     if (threadIdx.x == 0) next = take_item(w.queue, q);
-    const int l = f.q_level[q];
-    // the pair's kPerPair samples s0 + j kBlock / 2.  The bounds test makes each
-    // sample a block of code of its own, so a wavefront gathers its samples one
-    // after the other (4 loads in flight) and the 7-8 resident wavefronts per
-    // SIMD overlap each other's waits; issuing all 16 loads at once doubles the
-    // registers, halves the resident wavefronts and is slower, since the CU's
-    // L1 already holds as many L2 misses in flight as it can.  Positions: lane
-    // side computes samples 2 k + side and both lanes take each from the lane
-    // that computed it (all lanes active); an odd last one both lanes compute.
-    const int s0 = (int)item * kItem + (threadIdx.x >> 1);
-    Pos ps[kPerPair];
-#pragma unroll
-    for (int k = 0; k < kPerPair / 2; ++k) {
-      const int sm = s0 + (2 * k + side) * (kBlock / 2);
-      const Pos mine = sample_pos(f, b, w, sm < S ? sm : S - 1);
-      ps[2 * k] = pos_from_pair_lane<0>(mine);
-      ps[2 * k + 1] = pos_from_pair_lane<1>(mine);
-    }
-    if (kPerPair & 1) {
-      const int sl = s0 + (kPerPair - 1) * (kBlock / 2);
-      ps[kPerPair - 1] = sample_pos(f, b, w, sl < S ? sl : S - 1);
-    }
-    // output entries of sample s0; sample j is kBlock / 2 entries further along
-    // the feature row and kBlock / 64 Jacobian blocks further (kBlock / 2 is a
-    // multiple of 32)
-    float* fo = w.feat + (int64_t)feat_row(f, l, side) * w.cap + s0;
-    uint32_t* jo = reinterpret_cast<uint32_t*>(w.jac) + jac_record(f, l, s0);
-    const int64_t jstep = (int64_t)(kBlock / 64) * 4 * (6 * f.lpg * 32) / 2;  // words
-    // the level's kind is uniform over the item: one branch, no per-lane selects
-    if (f.dense[l]) {
-#pragma unroll
-      for (int j = 0; j < kPerPair; ++j)  // pairs leave together
-        if (s0 + j * (kBlock / 2) < S)
-          encode_level<F16, GRAD, 1>(f, l, ps[j], side, fo + j * (kBlock / 2), jo + j * jstep);
+    const int q_first = f.q_first[q], q_count = f.q_first[q + 1] - q_first;
+    if (hashed) {
+      const int first = (int)item * kItem + wave * kPerWave;
+      if (first < S) hashed_item<F16, GRAD>(f, w, s_rec[wave], lane, first, S, q_first, q_count);
     } else {
-#pragma unroll
-      for (int j = 0; j < kPerPair; ++j)
-        if (s0 + j * (kBlock / 2) < S)
-          encode_level<F16, GRAD, 2>(f, l, ps[j], side, fo + j * (kBlock / 2), jo + j * jstep);
+      const int first = (int)item * kDenseItem + wave * 64;
+      if (first < S) dense_item<F16, GRAD>(f, w, s_rec[wave], lane, first, S, q_first, q_count);
     }
     buf ^= 1;
     if (threadIdx.x == 0) s_item[buf] = next;
     __syncthreads();
-    item = s_item[buf];
+    item = __builtin_amdgcn_readfirstlane(s_item[buf]);
   }
 }
 
@@ -428,15 +690,22 @@ __global__ __launch_bounds__(kBlock) void k_occupancy(DevField f, uint32_t* bits
 
 }  // namespace
 
-int encode_blocks(const DevField& f, int n_cu, int per_cu) {
-  // per_cu blocks of 256 threads per CU (the work queues balance whatever is
-  // resident)
-  (void)f;
-  return n_cu * per_cu;
+// Blocks for a batch of up to max_samples samples: no more than its work items,
+// and 4 per CU where the resident blocks (n_blocks, 7 per CU) would take fewer
+// than 64 items each: what every block spends on finding the queues drained is
+// then a share of the kernel (800 k samples on 16 levels: 224 us with 4 blocks
+// per CU, 242 us with 7; 39 M samples: 8.10 ms and 7.90 ms).
+static int useful_blocks(const DevField& f, int64_t max_samples, int n_blocks, int n_cu) {
+  const int64_t items = (max_samples + kItem - 1) / kItem * f.n_hashed_queue +
+                        (max_samples + kDenseItem - 1) / kDenseItem * (f.n_queue - f.n_hashed_queue);
+  if (items < (int64_t)n_blocks * 64) n_blocks = std::min(n_blocks, 4 * n_cu);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(n_blocks, items));
 }
 
-hipError_t launch_encode(const DevField& f, const DevBatch& b, const DevWork& w, int n_blocks,
-                         int with_grad, hipStream_t s) {
+hipError_t launch_encode(const DevField& f, const DevBatch& b, const DevWork& w,
+                         int64_t max_samples, int n_blocks, int n_cu, int with_grad,
+                         hipStream_t s) {
+  n_blocks = useful_blocks(f, max_samples, n_blocks, n_cu);
   if (f.f16) {
     if (with_grad)
       hipLaunchKernelGGL((k_encode<true, true>), dim3(n_blocks), dim3(kBlock), 0, s, f, b, w);
@@ -449,6 +718,14 @@ hipError_t launch_encode(const DevField& f, const DevBatch& b, const DevWork& w,
       hipLaunchKernelGGL((k_encode<false, false>), dim3(n_blocks), dim3(kBlock), 0, s, f, b, w);
   }
   return hipGetLastError();
+}
+
+int encode_blocks_per_cu(const DevField& f) {
+  int n = 0;
+  const hipError_t e =
+      f.f16 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_encode<true, true>, kBlock, 0)
+            : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_encode<false, true>, kBlock, 0);
+  return e == hipSuccess && n > 0 ? n : 4;
 }
 
 hipError_t launch_occupancy(const DevField& f, uint32_t* bits, int R, float thr, hipStream_t s) {

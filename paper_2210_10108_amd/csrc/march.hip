@@ -18,13 +18,14 @@ constexpr int kScanBlock = 256;    // rays per block of the offset scan
 
 struct RayGeom {
   float o[3], d[3], tn, tf, delta;
-  float de[3];  // exact direction minus d (for compensated sample positions)
   int hit;
 };
 
 // Pixel -> ray (Sec. IV-A: the ray origin is the camera centre) and its
-// clip against the scene box.
-__device__ inline RayGeom make_ray(const DevField& f, const DevBatch& b, int ray) {
+// clip against the scene box.  D: the same direction in double, with which the
+// encoding places samples more precisely than float allows (decisions stay on
+// the float values).
+__device__ inline RayGeom make_ray(const DevField& f, const DevBatch& b, int ray, double D[3]) {
   RayGeom g;
   const float* pose = b.poses + 12 * (ray / b.P);
   int pix = b.pix[ray];
@@ -43,18 +44,15 @@ __device__ inline RayGeom make_ray(const DevField& f, const DevBatch& b, int ray
                                  __fmul_rn(dw[2], dw[2])));
   for (int a = 0; a < 3; ++a) g.d[a] = __fdiv_rn(dw[a], n);
   {
-    // the same direction in double: its difference from d lets the shading
-    // kernels place samples more precisely than float allows (decisions above
-    // stay on the float values)
     double xd = ((double)u + 0.5 - (double)b.cx) / (double)b.fx;
     double yd = ((double)v + 0.5 - (double)b.cy) / (double)b.fy;
-    double e[3], nn = 0.0;
+    double nn = 0.0;
     for (int a = 0; a < 3; ++a) {
-      e[a] = (double)pose[4 * a] * xd + (double)pose[4 * a + 1] * yd + (double)pose[4 * a + 2];
-      nn += e[a] * e[a];
+      D[a] = (double)pose[4 * a] * xd + (double)pose[4 * a + 1] * yd + (double)pose[4 * a + 2];
+      nn += D[a] * D[a];
     }
     nn = sqrt(nn);
-    for (int a = 0; a < 3; ++a) g.de[a] = (float)(e[a] / nn - (double)g.d[a]);
+    for (int a = 0; a < 3; ++a) D[a] /= nn;
   }
   float t_entry = -INFINITY, t_exit = INFINITY;
   bool empty = false;
@@ -170,13 +168,9 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_setup(DevField f, DevBatch b,
   const int ray = blockIdx.x * kRayBlock + threadIdx.x;
   int c = 0;
   if (ray < b.n_rays) {
-    const RayGeom g = make_ray(f, b, ray);
-    w.rdx[ray] = g.d[0];
-    w.rdy[ray] = g.d[1];
-    w.rdz[ray] = g.d[2];
-    w.rex[ray] = g.de[0];
-    w.rey[ray] = g.de[1];
-    w.rez[ray] = g.de[2];
+    double D[3];
+    const RayGeom g = make_ray(f, b, ray, D);
+    store_ray(w.rrec, ray, g.o, g.d, D);
     float sh[16];
     sh16(g.d, sh);
     float4* o = reinterpret_cast<float4*>(w.rsh + (size_t)16 * ray);
@@ -200,15 +194,12 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_setup(DevField f, DevBatch b,
 }
 
 // The stored geometry of a ray (hit = the clip left an interval).
-__device__ inline RayGeom stored_ray(const DevBatch& b, const DevWork& w, int ray) {
+__device__ inline RayGeom stored_ray(const DevWork& w, int ray) {
   RayGeom g;
-  const float* pose = b.poses + 12 * (ray / b.P);
-  g.o[0] = pose[3];
-  g.o[1] = pose[7];
-  g.o[2] = pose[11];
-  g.d[0] = w.rdx[ray];
-  g.d[1] = w.rdy[ray];
-  g.d[2] = w.rdz[ray];
+  const float4* r = w.rrec + 3 * (int64_t)ray;
+  const RayRecord rec = {r[0], r[1], {}};
+  rec.origin(g.o);
+  rec.dir(g.d);
   g.tn = w.rtn[ray];
   g.tf = w.rtf[ray];
   g.delta = w.rdelta[ray];
@@ -225,7 +216,7 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_count(DevField f, DevBatch b,
   for (int q = 0; q < kRaysPerWave; ++q) {
     int ray = wave * kRaysPerWave + q;
     if (ray >= b.n_rays) break;
-    const RayGeom g = stored_ray(b, w, ray);
+    const RayGeom g = stored_ray(w, ray);
     int n = march_wave<false>(f, g, lane, f.max_per_ray, nullptr, nullptr, nullptr, ray);
     if (lane == 0) w.count[ray] = n;
   }
@@ -325,7 +316,7 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_write(DevField f, DevBatch b,
     if (RAW) *wb.total = total;  // the counted batch's total (read back on demand)
   }
   // the encoding of this chunk, next on the stream, starts from empty work queues
-  if (blockIdx.x == 0 && threadIdx.x < kMaxLevels) wc.queue[threadIdx.x * kQueueStride] = 0u;
+  if (blockIdx.x == 0 && threadIdx.x <= kMaxLevels) wc.queue[threadIdx.x * kQueueStride] = 0u;
   // every load the wavefront's rays need is issued before the first is
   // marched (a ray past the end loads the last ray's values and is skipped);
   // each wavefront reads only its own rays' offsets, which it then overwrites
@@ -339,7 +330,7 @@ __global__ __launch_bounds__(kRayBlock) void k_ray_write(DevField f, DevBatch b,
     const int before = RAW ? __shfl(raw_excl, rb / kScanBlock) : wb.blocksum[rb / kScanBlock];
     off[q] = before + wb.off[rb] - sample_base;
     cnt[q] = wc.count[rc];
-    geo[q] = stored_ray(b, wc, rc);
+    geo[q] = stored_ray(wc, rc);
   }
 #pragma unroll
   for (int q = 0; q < kRaysPerWave; ++q) {

@@ -250,12 +250,16 @@ struct Arith<true> {
   __device__ static __forceinline__ const Unit* bwd(const DevField& f) { return f.hbwd; }
 };
 
+// Unit direction of a ray, from its record.
+__device__ __forceinline__ void ray_dir(const DevWork& w, int ray, float d[3]) {
+  const float4* r = w.rrec + 3 * (int64_t)ray;
+  const RayRecord rec = {r[0], r[1], {}};
+  rec.dir(d);
+}
+
 // Unit ray direction of sample s.
 __device__ __forceinline__ void sample_dir(const DevWork& w, int s, float d[3]) {
-  int ray = w.sray[s];
-  d[0] = w.rdx[ray];
-  d[1] = w.rdy[ray];
-  d[2] = w.rdz[ray];
+  ray_dir(w, w.sray[s], d);
 }
 
 // Mask bits of a ReLU layer's 16 values t[m][i] of one column tile (unit
@@ -540,8 +544,8 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
   }
   // d loss / d p = sum over the lane group's levels 4j + g of d loss / d
   // feature times the stored Jacobian, then over the 4 groups.  This lane
-  // group's Jacobian records of the sample (level 4j + g at record j): six
-  // fp16 values d feature_q / d pos_a at 3 q + a
+  // group's Jacobian records of the sample (level 4j + g at record j), six
+  // fp16 values each
   const uint32_t* jp = reinterpret_cast<const uint32_t*>(w.jac) +
                        (((int64_t)(sc >> 5) * 4 + g) * (6 * LPG * 32) + (sc & 31) * 6) / 2;
   gx[0] = gx[1] = gx[2] = 0.f;
@@ -552,10 +556,12 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
     // read once: non-temporal, so that they do not displace cached data
     const uint32_t r[3] = {__builtin_nontemporal_load(rec), __builtin_nontemporal_load(rec + 1),
                            __builtin_nontemporal_load(rec + 2)};
-    float J[6];
+    float J[6];  // d feature_q / d pos_a at 3 q + a; record: (q, a) = (0, 0) (0, 1),
+                 // (1, 0) (1, 1), (0, 2) (1, 2)
+    constexpr int at[6] = {0, 1, 3, 4, 2, 5};
 #pragma unroll
     for (int k = 0; k < 6; ++k)
-      J[k] = __half2float(__ushort_as_half((unsigned short)(r[k / 2] >> (16 * (k % 2)))));
+      J[at[k]] = __half2float(__ushort_as_half((unsigned short)(r[k / 2] >> (16 * (k % 2)))));
     float gl[3] = {0.f, 0.f, 0.f};
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -715,7 +721,8 @@ __global__ __launch_bounds__(kBlock) void k_ray_bwd(DevField f, DevBatch b, DevW
     }
 
     // pass 2: the composite backward, step by step, and the networks
-    const float d[3] = {w.rdx[ray], w.rdy[ray], w.rdz[ray]};
+    float d[3];
+    ray_dir(w, ray, d);
     float R[3] = {C[0], C[1], C[2]};  // colour behind the step (background included)
     float carry2 = 0.0f;
     float M[3] = {0.f, 0.f, 0.f}, G[3] = {0.f, 0.f, 0.f};  // this column's share of the sums

@@ -23,6 +23,8 @@ constexpr int64_t kDeviceSizedBytes = (int64_t)16 << 30;  // worst-case sample b
                                                            // gradient may allocate to skip the
                                                            // host's read of the sample totals
 constexpr int kReduceParts = 64;      // parts per hypothesis of the reduction (lanes of one wave)
+constexpr int64_t kGroupBytes = (int64_t)4 << 20;  // level tables one encoding work queue may
+                                                   // span: an XCD's L2
 constexpr int kAdamState = 16;        // Adam state floats per hypothesis: m[6], v[6], n, 3 pads
 
 // A operand of one (row tile, K step) of v_mfma_f32_16x16x32_bf16: 8 bf16
@@ -75,7 +77,7 @@ __device__ inline void sh16(const float d[3], float v[16]) {
 // The value of the partner lane (lane ^ 1).  Both lanes must be active.
 __device__ __forceinline__ float lane_pair_swap(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1 /* quad_perm
-                                                    [1,0,3,2] */, 0xF, 0xF, false));
+                                                    [1,0,3,2] */, 0xF, 0xF, true));
 }
 
 // Inclusive prefix sum over the 64 lanes of a wavefront, all lanes active:
@@ -103,7 +105,9 @@ struct DevField {
   uint32_t dense[kMaxLevels];   // 1: vertex index i + j n1 + k n1^2
   uint32_t n1[kMaxLevels];      // res + 1
   int32_t f16;                  // table stored as fp16
-  int32_t q_level[kMaxLevels];  // level served by encoding work queue q (hashed levels first)
+  int32_t q_level[kMaxLevels];  // levels in the order of the encoding's work queues, hashed first
+  int32_t q_first[kMaxLevels + 1];  // queue q serves q_level[q_first[q] .. q_first[q + 1] - 1]
+  int32_t n_queue, n_hashed_queue;  // work queues; the first n_hashed_queue serve hashed levels
   const float* table32;         // [L][T][2]
   const __half* table16;        // [L][T][2]
   const WeightUnit* wfwd;       // forward A-operand tiles [kFwdUnits]
@@ -118,7 +122,7 @@ struct DevField {
   uint32_t bf16_neg1[2];        // bf16 pairs (-1, 0) and (0, -1): the MLP kernels' split
                                 // multipliers, read as data (see split2 in mlp.hip)
   float mn[3], mx[3], inv_ext[3];
-  float inv_ext_err[3];         // inv_ext * extent - 1 (relative rounding of the reciprocal)
+  double inv64[3], mn64[3];     // 1 / extent and the box corner in double
   int32_t march_mode, n_uniform;
   float step;
   int32_t max_samples;
@@ -132,6 +136,35 @@ struct DevField {
   int32_t max_per_ray;          // hard cap on kept samples per ray (buffer bound)
 };
 
+// A ray's record: three float4, so that a kernel that looks rays up by sample
+// takes one address and three 16-byte loads: (o, d_x), (d_y, d_z, D_x),
+// (D_y, D_z) with D the unit direction in double.
+struct RayRecord {
+  float4 a, b, c;
+  __device__ __forceinline__ void origin(float o[3]) const { o[0] = a.x, o[1] = a.y, o[2] = a.z; }
+  __device__ __forceinline__ void dir(float d[3]) const { d[0] = a.w, d[1] = b.x, d[2] = b.y; }
+  __device__ __forceinline__ void dir64(double D[3]) const {
+    D[0] = __hiloint2double(__float_as_int(b.w), __float_as_int(b.z));
+    D[1] = __hiloint2double(__float_as_int(c.y), __float_as_int(c.x));
+    D[2] = __hiloint2double(__float_as_int(c.w), __float_as_int(c.z));
+  }
+};
+
+__device__ __forceinline__ RayRecord load_ray(const float4* rrec, int ray) {
+  const float4* r = rrec + 3 * (int64_t)ray;
+  return {r[0], r[1], r[2]};
+}
+
+__device__ __forceinline__ void store_ray(float4* rrec, int ray, const float o[3],
+                                          const float d[3], const double D[3]) {
+  float4* r = rrec + 3 * (int64_t)ray;
+  auto lo = [](double x) { return __int_as_float(__double2loint(x)); };
+  auto hi = [](double x) { return __int_as_float(__double2hiint(x)); };
+  r[0] = make_float4(o[0], o[1], o[2], d[0]);
+  r[1] = make_float4(d[1], d[2], lo(D[0]), hi(D[0]));
+  r[2] = make_float4(lo(D[1]), hi(D[1]), lo(D[2]), hi(D[2]));
+}
+
 struct DevBatch {
   int32_t K, P, n_rays;         // hypotheses, pixels per hypothesis, K*P (this chunk)
   const float* poses;           // [K][12]
@@ -142,9 +175,10 @@ struct DevBatch {
 };
 
 struct DevWork {
-  // per ray (SoA)
-  float *rdx, *rdy, *rdz, *rtn, *rtf, *rdelta;
-  float *rex, *rey, *rez;       // direction correction: exact unit direction - (rdx, rdy, rdz)
+  // per ray (SoA, and one record)
+  float4* rrec;                 // [n_rays][3] ray record: origin o and float unit direction d, then
+                                // the unit direction in double (ray_record)
+  float *rtn, *rtf, *rdelta;
   float* rsh;                   // [n_rays][16] SH basis of each ray's direction (sh16)
   int32_t* count;               // kept samples per ray
   int32_t* off;                 // counted batch: offset inside each 256-ray block;
@@ -165,9 +199,10 @@ struct DevWork {
   __half* jac;                  // [6L][cap] d feature / d pos: 12-byte records per sample and
                                 // level in 32-sample blocks (jac_record in encode.hip)
   int64_t cap;                  // sample capacity (row stride of feat and jac)
-  uint32_t* queue;              // [kMaxLevels * kQueueStride] encoding work-queue counters
-                                // (word q * kQueueStride: items of queue q taken), zeroed by
-                                // k_ray_write before every encoding of the chunk
+  uint32_t* queue;              // [(kMaxLevels + 1) * kQueueStride] encoding work-queue counters
+                                // (word q * kQueueStride: items of queue q taken) and, last, the
+                                // bits of the queues known to be drained; zeroed by k_ray_write
+                                // before every encoding of the chunk
 };
 
 // ---- launchers (all enqueue on `s`, no synchronisation)
@@ -178,8 +213,10 @@ hipError_t launch_march_count(const DevField& f, const DevBatch& b, const DevWor
 hipError_t launch_march_write(const DevField& f, const DevBatch& b, const DevWork& wb,
                               const DevWork& wc, int ray_base, int sample_base, int chunk_total,
                               int raw_blocks, int32_t* lattice_j_out, hipStream_t s);
-hipError_t launch_encode(const DevField& f, const DevBatch& b, const DevWork& w, int n_blocks,
-                         int with_grad, hipStream_t s);
+// max_samples: what the batch may hold at most (no more blocks than its work items)
+hipError_t launch_encode(const DevField& f, const DevBatch& b, const DevWork& w,
+                         int64_t max_samples, int n_blocks, int n_cu, int with_grad,
+                         hipStream_t s);
 hipError_t launch_mlp_fwd(const DevField& f, const DevBatch& b, const DevWork& w, int n_blocks,
                           int with_grad, hipStream_t s);
 hipError_t launch_composite(const DevField& f, const DevBatch& b, const DevWork& w, int with_grad,
@@ -218,6 +255,6 @@ int reduce_parts(int K);
 int mlp_fwd_blocks_per_cu(int lpg, int f16);
 int mlp_bwd_blocks_per_cu(int lpg, int sh_dir_grad, int f16);
 int ray_bwd_blocks_per_cu(int lpg, int sh_dir_grad, int f16);
-int encode_blocks(const DevField& f, int n_cu, int per_cu);
+int encode_blocks_per_cu(const DevField& f);
 
 }  // namespace pnerf
