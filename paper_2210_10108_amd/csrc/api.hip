@@ -207,7 +207,8 @@ U_t build_fwd_units(const Weights& W, int lpg) {
       for (int s2 = 0; s2 < 2; ++s2) {
         const int u = kpos(s2, g, j);
         U.put(kFD2 + s2, lane, j, W.D2(u, r));
-        U.put(kFC3 + s2, lane, j, r < 3 ? W.C3(u, r) : 0.0f);
+        // colour 3: logit q in row 4 (q + 1), the first row of lane group q + 1
+        U.put(kFC3 + s2, lane, j, r >= 4 && r % 4 == 0 ? W.C3(u, r / 4 - 1) : 0.0f);
         for (int m = 0; m < 4; ++m) U.put(kFC2 + 2 * m + s2, lane, j, W.C2(u, 16 * m + r));
       }
     }
@@ -1164,9 +1165,7 @@ pnerf_status pnerf_field_inspect(pnerf_field* F, int32_t what, float* dst, int64
   if (what > 0 && !F->last_keeps_samples)
     return fail(PNERF_ERR_INVALID_ARG,
                 "the last loss gradient kept no per-sample intermediates (backward = 1)");
-  DevWork w{};
-  carve_samples(F->dev, F->samp_cap, &w, (char*)F->d_samp[0]);
-  w.total = F->d_totals;  // the single chunk of the last call
+  const DevWork w = chunk_work(F, 0, 0, 0);  // the single chunk of the last call
   HIP_TRY(launch_inspect(F->dev, DevBatch{}, w, what, dst, n, (hipStream_t)stream));
   return PNERF_OK;
 }

@@ -126,13 +126,25 @@ __global__ __launch_bounds__(kBlock) void k_composite(DevField f, DevBatch b, De
   }
 }
 
-// Torque and force terms of one sample (Eq. 3 and Eq. 2 before the sums), as
-// the MLP backward kernel left them in rows 0..5 of the feature array.
+// Torque and force terms of one sample (Eq. 3 and Eq. 2 before the sums): the
+// MLP backward kernel left its force dL/dp in rows 0..2 of the feature array,
+// and on the direction path dL/dd in rows 3..5; the torque is
+// d x (t dL/dp + dL/dd).
 __device__ __forceinline__ void sample_terms(const DevField& f, const DevWork& w, int s,
                                              float out[6]) {
-  (void)f;
+  const float t = w.t[s];
+  const float4* r = w.rrec + 3 * (int64_t)w.sray[s];
+  const RayRecord rec = {r[0], r[1], {}};
+  float d[3], m[3];
+  rec.dir(d);
 #pragma unroll
-  for (int q = 0; q < 6; ++q) out[q] = w.feat[(int64_t)q * w.cap + s];
+  for (int a = 0; a < 3; ++a) {
+    out[3 + a] = w.feat[(int64_t)a * w.cap + s];
+    m[a] = t * out[3 + a] + (f.sh_dir_grad ? w.feat[(int64_t)(3 + a) * w.cap + s] : 0.0f);
+  }
+  out[0] = d[1] * m[2] - d[2] * m[1];
+  out[1] = d[2] * m[0] - d[0] * m[2];
+  out[2] = d[0] * m[1] - d[1] * m[0];
 }
 
 // Per-hypothesis reduction in two fixed-order stages.  Block (j, k) sums part

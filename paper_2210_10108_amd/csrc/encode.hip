@@ -28,9 +28,13 @@
 // queue per dense level; with every gather in L1 it took 5.0 ms, without
 // gathers 4.2 ms.
 //
-// Features are stored SoA, row p = (l % 4) * 2 LPG + (l / 4) * 2 + q for
-// feature q of level l (the order in which the MLP kernels feed them to MFMA),
-// row stride = the workspace sample capacity.  The Jacobian d feature /
+// Features are stored by blocks of 16 samples (a column tile of the MLP
+// kernels): block b, lane group g = l % 4, level l / 4 of the group, sample
+// s % 16, feature q at ((4 b + g) LPG + l / 4) 32 + (s % 16) 2 + q.  A level's
+// share of a block is one cache line, written by one instruction, and a lane of
+// the network kernel reads a level's two features with one 8-byte load at a
+// constant offset from its tile (rows of one feature each took twice the loads
+// and an address each).  The Jacobian d feature /
 // d pos of every level (pos = x N_l: bounded by the table's value
 // differences, zero along clamped components) is stored in fp16 (rounding
 // below 2^-11 of each entry), as one 12-byte record per sample and level: three
@@ -49,6 +53,7 @@ namespace pnerf {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int kFeatBlock = 16 * 8;  // bytes of one level's features of a 16-sample block
 constexpr int kJacBlock = 32 * 12;  // bytes of one level's Jacobian records of a 32-sample block
 constexpr uint32_t kPrime1 = 2654435761u, kPrime2 = 805459861u;
 
@@ -268,29 +273,32 @@ __device__ __forceinline__ void blend_yz(const float2 e[4], const float wt[3], f
 }
 
 // Where a level's outputs go, from a uniform sample index `first` (a multiple of
-// 32): the entries of feature rows q = 0, 1 and of the Jacobian records.  A lane
-// adds a 32-bit byte offset (record_offset for the records), so that the stores
-// take a scalar base each and no 64-bit addresses per lane.
+// 32): the level's features and its Jacobian records.  A lane adds a 32-bit byte
+// offset (feature_offset, record_offset), so that the stores take a scalar base
+// each and no 64-bit addresses per lane.
 typedef __attribute__((address_space(1))) char* global_ptr;
 struct LevelOut {
-  global_ptr feat[2], jac;
+  global_ptr feat, jac;
 };
 
 __device__ __forceinline__ LevelOut level_out(const DevField& f, const DevWork& w, int l,
                                               int first) {
-  const int64_t row = (l & 3) * 2 * f.lpg + (l >> 2) * 2;
+  const int slot = (l & 3) * f.lpg + (l >> 2);
   LevelOut o;
-  o.feat[0] = (global_ptr)(w.feat + row * w.cap + first);
-  o.feat[1] = (global_ptr)(w.feat + (row + 1) * w.cap + first);
-  o.jac = (global_ptr)w.jac +
-          ((int64_t)(first >> 5) * 4 * f.lpg + (l & 3) * f.lpg + (l >> 2)) * kJacBlock;
+  o.feat = (global_ptr)w.feat + ((int64_t)(first >> 4) * 4 * f.lpg + slot) * kFeatBlock;
+  o.jac = (global_ptr)w.jac + ((int64_t)(first >> 5) * 4 * f.lpg + slot) * kJacBlock;
   // opaque, or the compiler adds the lane's offset to the arrays' bases first
   // and carries 64-bit lane addresses through the whole kernel
-  asm("" : "+s"(o.feat[0]), "+s"(o.feat[1]), "+s"(o.jac));
+  asm("" : "+s"(o.feat), "+s"(o.jac));
   return o;
 }
 
-// Byte offset of sample first + i's record from LevelOut::jac.
+// Byte offset of sample first + i's features from LevelOut::feat, and of its
+// record from LevelOut::jac.
+__device__ __forceinline__ uint32_t feature_offset(const DevField& f, int i) {
+  return (uint32_t)((i >> 4) * 4 * f.lpg * kFeatBlock + (i & 15) * 8);
+}
+
 __device__ __forceinline__ uint32_t record_offset(const DevField& f, int i) {
   return (uint32_t)((i >> 5) * 4 * f.lpg * kJacBlock + (i & 31) * 12);
 }
@@ -435,7 +443,9 @@ __device__ __forceinline__ void hashed_item(const DevField& f, const DevWork& w,
                                             int lane, int first, int S, int q_first, int q_count) {
   const int side = lane & 1;
   const int own = 32 * side + (lane >> 1);  // this lane's sample of step k: first + own + 64 k
-  const uint32_t so = own * 4, jo = record_offset(f, own);
+  // feature `side` of sample i of runs 2 k and 2 k + 1; the own sample's record
+  const uint32_t fo = feature_offset(f, lane >> 1) + 4 * side;
+  const uint32_t run = feature_offset(f, 32), jo = record_offset(f, own);
   float t[2];
   int ray[2];
 #pragma unroll
@@ -479,16 +489,10 @@ __device__ __forceinline__ void hashed_item(const DevField& f, const DevWork& w,
     for (int k = 0; k < 2; ++k) {
       const Part p0 = finish_part<GRAD>(e[0], wt[0], side);
       const Part p1 = finish_part<GRAD>(e[1], wt[1], side);
-      // side q completes its own sample (run 2 k + q): it hands the partner its
-      // part of the other one.  Record: axes 0 and 1 of feature 0, the same of
-      // feature 1, axis 2 of both
-      float fq[2];
+      // side q completes the record of its own sample (run 2 k + q) and hands
+      // the partner its part of the other one: axes 0 and 1 of feature 0, the
+      // same of feature 1, axis 2 of both
       uint32_t r[3];
-      {
-        const float kept = side ? p1.feat : p0.feat, got = lane_pair_swap(side ? p0.feat : p1.feat);
-        fq[0] = side ? got : kept;
-        fq[1] = side ? kept : got;
-      }
       if (GRAD) {
         const uint32_t k01 = side ? p1.j01 : p0.j01, g01 = pair_swap_u(side ? p0.j01 : p1.j01);
         const uint32_t k2 = side ? p1.j2 : p0.j2, g2 = pair_swap_u(side ? p0.j2 : p1.j2);
@@ -499,8 +503,8 @@ __device__ __forceinline__ void hashed_item(const DevField& f, const DevWork& w,
       }
       if (first + 64 * k < S) {
         const LevelOut o = level_out(f, w, l, first + 64 * k);
-        stream_out(o.feat[0], so, fq[0]);
-        stream_out(o.feat[1], so, fq[1]);
+        stream_out(o.feat, fo, p0.feat);
+        stream_out(o.feat, fo + run, p1.feat);
         if (GRAD) {
 #pragma unroll
           for (int a = 0; a < 3; ++a) stream_out(o.jac, jo + 4 * a, r[a]);
@@ -524,7 +528,7 @@ __device__ __forceinline__ void dense_item(const DevField& f, const DevWork& w, 
   const uint32_t at = (uint32_t)min(lane, S - 1 - first);
   const int ray = (w.sray + first)[at];
   const float t = (w.t + first)[at];
-  const uint32_t so = lane * 4, jo = record_offset(f, lane);
+  const uint32_t fo = feature_offset(f, lane), jo = record_offset(f, lane);
   uint32_t clamped;
   const Pos ps = sample_pos(f, t, wave_record(w, lds, lane, ray, __builtin_amdgcn_readfirstlane(ray),
                                               __builtin_amdgcn_readlane(ray, 63)), clamped);
@@ -565,8 +569,9 @@ __device__ __forceinline__ void dense_item(const DevField& f, const DevWork& w, 
       }
     }
     const LevelOut o = level_out(f, w, l, first);
-    stream_out(o.feat[0], so, feat[0]);
-    stream_out(o.feat[1], so, feat[1]);
+    typedef float float2_t __attribute__((ext_vector_type(2)));
+    const float2_t both = {feat[0], feat[1]};
+    stream_out(o.feat, fo, both);
     if (GRAD) {
       uint32_t r[3] = {pack_half2(j[0][0], j[0][1]), pack_half2(j[1][0], j[1][1]),
                        pack_half2(j[0][2], j[1][2])};

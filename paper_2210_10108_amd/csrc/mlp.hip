@@ -29,8 +29,15 @@
 // position j of step s -- is baked into the weight tiles built at field
 // creation, which each workgroup stages in LDS (hi and lo parts).
 // Lane group g reads the features of levels g, g+4, g+8, g+12 of its column's
-// sample (rows 2 LPG g .. of the SoA feature array): the first layer's B
-// operand.
+// sample, one 8-byte load per level from its column tile's block of the feature
+// array: the first layer's B operand.
+//
+// What bounds the kernels: the weight units' LDS reads (40 of 16 bytes per lane
+// and tile, 8 cycles each at 128 B a cycle for the CU's four SIMDs together:
+// 64% of the forward's time), the vector work (254 instructions per tile beside
+// 60 MFMA products, 50%) and the matrix pipe (48%), whose phases alternate
+// within a wavefront and overlap only across the 8 resident ones; the texture
+// unit takes 16 cycles for every load or store instruction.
 #include <algorithm>
 
 #include "pnerf_internal.h"
@@ -48,7 +55,7 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kBlock = 512;  // 8 wavefronts: one LDS copy of the weight units serves 8 waves
 constexpr int kFwdNT = 1;    // 16-sample column tiles per wavefront, forward
-constexpr int kBwdNT = 1;    // and backward (68 registers without the SH direction path: 7 wavefronts per SIMD)
+constexpr int kBwdNT = 1;    // and backward (62 registers without the SH direction path: 8 wavefronts per SIMD)
 
 struct Split {
   bf16x8 hi, lo;
@@ -117,6 +124,14 @@ __device__ __forceinline__ Split load_unit(const WeightUnit* lds, int u, int lan
   return s;
 }
 
+// 1 in each half of the result whose half of x is nonzero (the compiler has no
+// builtin for the packed minimum and expands the generic one into compares).
+__device__ __forceinline__ uint32_t nonzero2(uint32_t x) {
+  uint32_t r;
+  asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(x), "s"(0x00010001u));
+  return r;
+}
+
 // The B operand of one K step from two accumulator tiles (rows of tile t0 at
 // positions 0..3, of tile t1 at 4..7) for a ReLU layer: relu(t0), relu(t1) and, when
 // MASK, its mask bits.  Position v of the K step is value pair p = v / 2:
@@ -124,9 +139,8 @@ __device__ __forceinline__ Split load_unit(const WeightUnit* lds, int u, int lan
 // max(bits, 0) as a signed integer is the ReLU (every non-positive float, -0
 // included, has a bit pattern <= 0); a unit counts as active when its hi part
 // is nonzero, which differs from x > 0 only for positive values below
-// 2^-133.  Both halves of the packed hi are then below 0x8000, so adding
-// 0x7FFF to each sets its top bit exactly when it is nonzero, without a carry
-// into the other half.
+// 2^-133: min(half, 1) of both halves of the packed hi in one instruction, then
+// one shift-or.
 template <bool MASK>
 __device__ __forceinline__ Split relu_pack2(const floatx4& t0, const floatx4& t1, const SplitK& k,
                                             uint32_t& mk, int shift) {
@@ -140,10 +154,7 @@ __device__ __forceinline__ Split relu_pack2(const floatx4& t0, const floatx4& t1
     split2(v[2 * p], v[2 * p + 1], k, h, l);
     hw[p] = h;
     lw[p] = l;
-    if (MASK) {
-      const uint32_t top = h + 0x7FFF7FFFu;  // bits 15 and 31: the halves are nonzero
-      mk |= (top >> (15 - shift - p)) & (0x00010001u << (shift + p));
-    }
+    if (MASK) mk |= nonzero2(h) << (shift + p);
   }
   Split s;
   s.hi = __builtin_bit_cast(bf16x8, hw);
@@ -216,8 +227,7 @@ struct Arith<true> {
     return {__builtin_bit_cast(f16x8, w)};
   }
   // relu as in relu_pack2; a unit counts as active when its fp16 value is
-  // nonzero (positive values below 2^-25 round to zero and count as off),
-  // found by the same carry-free add: both halves are below 0x8000
+  // nonzero (positive values below 2^-25 round to zero and count as off)
   template <bool MASK>
   __device__ static __forceinline__ Op relu_pack(const floatx4& t0, const floatx4& t1,
                                                  const SplitK&, uint32_t& mk, int shift) {
@@ -229,10 +239,7 @@ struct Arith<true> {
     for (int p = 0; p < 4; ++p) {
       const uint32_t h = half2_rn(v[2 * p], v[2 * p + 1]);
       w[p] = h;
-      if (MASK) {
-        const uint32_t top = h + 0x7FFF7FFFu;
-        mk |= (top >> (15 - shift - p)) & (0x00010001u << (shift + p));
-      }
+      if (MASK) mk |= nonzero2(h) << (shift + p);
     }
     return {__builtin_bit_cast(f16x8, w)};
   }
@@ -272,8 +279,47 @@ __device__ __forceinline__ void apply_mask(floatx4 (&t)[4], uint32_t mk, int bas
     for (int i = 0; i < 4; ++i) {
       const int v = 4 * m + i;
       const int bit = base + 4 * (v / 8) + (v % 8) / 2 + 16 * (v & 1);
-      if (!((mk >> bit) & 1u)) t[m][i] = 0.0f;
+      // the bit spread over a word (one bit-field extract), and one AND
+      int on;
+      asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(on) : "v"(mk), "n"(bit));
+      t[m][i] = __int_as_float(__float_as_int(t[m][i]) & on);
     }
+}
+
+// Rows of 16 lanes exchanged between two registers: from (r0, r1, r2, r3) twice,
+// swap16 gives (r0, r0, r2, r2) and (r1, r1, r3, r3), swap32 gives (r0, r1, r0,
+// r1) and (r2, r3, r2, r3).
+__device__ __forceinline__ void swap16(float x, float& even, float& odd) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  even = __uint_as_float(r[0]);
+  odd = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap32(float x, float& lo, float& hi) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  lo = __uint_as_float(r[0]);
+  hi = __uint_as_float(r[1]);
+}
+
+// Sum of the four lane groups' values, in every group (as adding the values of
+// lanes l ^ 16, then l ^ 32).
+__device__ __forceinline__ float group_sum(float x) {
+  float a, b;
+  swap16(x, a, b);
+  swap32(a + b, a, b);
+  return a + b;
+}
+
+// Stage W_c3 by lane group: unit 16 m + 4 g + i at [g][4 m + i].
+__device__ __forceinline__ void stage_c3(const DevField& f, float (*s_c3)[16][3]) {
+  for (int i = threadIdx.x; i < 64 * 3; i += kBlock) {
+    const int u = i / 3;
+    s_c3[(u >> 2) & 3][(u >> 4) * 4 + (u & 3)][i % 3] = f.wc3[i];
+  }
+}
+
+// Stage the level resolutions as floats, by lane group: level 4 j + g at [g][j].
+__device__ __forceinline__ void stage_res(const DevField& f, float (*s_res)[4]) {
+  if (threadIdx.x < kMaxLevels) s_res[threadIdx.x & 3][threadIdx.x >> 2] = (float)f.res[threadIdx.x];
 }
 
 // Gradient of SH functions 4g..4g+3 w.r.t. the direction, contracted with gs.
@@ -310,6 +356,9 @@ __device__ inline void sh4_vjp(const float d[3], int g, const float gs[4], float
 }
 
 // ------------------------------------------------------------------ forward
+// 39.5 M samples of 16 levels: 2.56 ms, 2.81 ms with mask bits from carries of
+// an addition (82 instructions against 48), features in rows (8 loads and their
+// addresses against 4) and all outputs in lane group 0.
 // GRAD = false (forward rendering only) skips the ReLU masks the backward
 // pass needs; it is a separate kernel so that profiles keep the two apart.
 template <int LPG, bool GRAD, bool H>
@@ -327,7 +376,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
   const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
   const int wave = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   const int n_waves = gridDim.x * (kBlock / 64);
-  const float* frow = w.feat + (int64_t)(g * KD) * w.cap;
+  // lane group g stores one of sigma, r, g, b (see the outputs below)
+  float* const out = g == 0 ? w.sig : g == 1 ? w.cr : g == 2 ? w.cg : w.cb;
+  const uint32_t lane_feat = g * LPG * 32 + col * 2;
   const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
   const SplitK sk = split_k(f);
 
@@ -343,9 +394,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
       const int s = tile * TS + nt * 16 + col;
       sidx[nt] = s;
       const int sc = s < S ? s : S - 1;
+      // the column's features of levels 4 j + g: two floats each (the encoding
+      // fills a batch's last columns too)
+      const float* ft = w.feat + (int64_t)(tile * NT + nt) * (4 * LPG * 32);
       float v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = j < KD ? frow[(int64_t)j * w.cap + sc] : 0.0f;
+      for (int j = 0; j < 4; ++j) {
+        const float2 x = j < LPG ? *reinterpret_cast<const float2*>(ft + lane_feat + 32 * j)
+                                 : make_float2(0.0f, 0.0f);
+        v[2 * j] = x.x;
+        v[2 * j + 1] = x.y;
+      }
       xf[nt] = A::pack(v, sk);
       // SH functions 4g..4g+3 of the sample's ray (sh16, stored per ray)
       const float4 sh = reinterpret_cast<const float4*>(w.rsh)[4 * w.sray[sc] + g];
@@ -417,7 +476,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         for (int nt = 0; nt < NT; ++nt) b2[nt][m] = A::mma(a, x[nt], b2[nt][m]);
       }
     }
-    // colour layer 3 on relu(b2) (3 outputs in rows 0..2)
+    // colour layer 3 on relu(b2) (3 outputs, in rows 4, 8 and 12)
     floatx4 z[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) z[nt] = zero;
@@ -430,26 +489,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                                                       mw1[nt], 4 * s2),
                        z[nt]);
     }
-    // outputs: rows 0..3 live in lane group 0
+    // outputs: lane group 0 holds h_0 and lane group q + 1 the colour logit q
+    // (row 4 (q + 1) of layer 3), so each lane evaluates and stores one value
+    // (all four in lane group 0: 4 stores, 4 exponentials and 3 reciprocals)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       const int s = sidx[nt];
-      if (g == 0 && s < S) {
-        // sigmoid with the hardware reciprocal (1 ulp)
-        w.sig[s] = __expf(h[nt][0] + f.density_bias);
-        w.cr[s] = __builtin_amdgcn_rcpf(1.0f + __expf(-z[nt][0]));
-        w.cg[s] = __builtin_amdgcn_rcpf(1.0f + __expf(-z[nt][1]));
-        w.cb[s] = __builtin_amdgcn_rcpf(1.0f + __expf(-z[nt][2]));
-      }
+      const float e = __expf(g == 0 ? h[nt][0] + f.density_bias : -z[nt][0]);
+      // sigmoid with the hardware reciprocal (1 ulp)
+      if (s < S) out[s] = g == 0 ? e : __builtin_amdgcn_rcpf(1.0f + e);
     }
     if (GRAD) {
       // two words per lane per 16-sample column tile
-      uint32_t* mw = w.masks + (size_t)tile * NT * 2 * 64 + lane;
+      uint2* mw = reinterpret_cast<uint2*>(w.masks) + (size_t)tile * NT * 64 + lane;
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        mw[(2 * nt) * 64] = mw0[nt];
-        mw[(2 * nt + 1) * 64] = mw1[nt];
-      }
+      for (int nt = 0; nt < NT; ++nt) mw[nt * 64] = make_uint2(mw0[nt], mw1[nt]);
     }
   }
 }
@@ -459,14 +513,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // the sample of column col.  In: z = d loss / d z of that sample (zero when it
 // has none), gh0 = d loss / d h_0 of that sample (in every lane group), the
 // sample's two ReLU mask words as the forward kernel stored them for this lane
-// group, and sc = the sample whose Jacobian records are read (any valid sample
+// group, s_res = the staged resolutions N_l (stage_res), and sc = the sample whose Jacobian records are read (any valid sample
 // when the column is empty).  Out: d loss / d p of the sample, gx (in every
 // lane group, after the sums over the groups), and on the direction path the
 // term d loss / d d through the SH input, gd (likewise summed).
 template <int LPG, bool DIR, bool H>
 __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
-                                         const typename Arith<H>::Unit* lds, const float* s_c3,
-                                         const SplitK& sk, int lane, const float zin[3],
+                                         const typename Arith<H>::Unit* lds, const float (*s_c3)[16][3],
+                                         const SplitK& sk, const float (*s_res)[4], int lane,
+                                         const float zin[3],
                                          float gh0in, uint32_t mw0, uint32_t mw1, int sc,
                                          const float d[3], float gx[3], float gd[3]) {
   using A = Arith<H>;
@@ -493,7 +548,7 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
   for (int m = 0; m < 4; ++m)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float* c3 = s_c3 + 3 * (16 * m + 4 * g + i);
+      const float* c3 = s_c3[g][4 * m + i];
       gb2[m][i] = c3[0] * z[0] + c3[1] * z[1] + c3[2] * z[2];
     }
   apply_mask(gb2, mw1, 0);
@@ -549,6 +604,8 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
   const uint32_t* jp = reinterpret_cast<const uint32_t*>(w.jac) +
                        (((int64_t)(sc >> 5) * 4 + g) * (6 * LPG * 32) + (sc & 31) * 6) / 2;
   gx[0] = gx[1] = gx[2] = 0.f;
+  const float4 r4 = *reinterpret_cast<const float4*>(s_res[g]);
+  const float res[4] = {r4.x, r4.y, r4.z, r4.w};
 #pragma unroll
   for (int j = 0; j < LPG; ++j) {
     // level 4j + g: d loss / d pos_l = sum_q gf * J, then times N_l
@@ -569,9 +626,8 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
 #pragma unroll
       for (int a = 0; a < 3; ++a) gl[a] += gq * J[3 * q + a];
     }
-    const float N = (float)f.res[4 * j + g];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) gx[a] += N * gl[a];
+    for (int a = 0; a < 3; ++a) gx[a] += res[j] * gl[a];
   }
   gd[0] = gd[1] = gd[2] = 0.f;
   if (DIR) {
@@ -580,19 +636,21 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
   }
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    gx[a] += __shfl_xor(gx[a], 16);
-    gx[a] += __shfl_xor(gx[a], 32);
-    gx[a] *= f.inv_ext[a] * unscale;  // d pos / d p = N_l / extent (N_l applied above)
-    gd[a] += __shfl_xor(gd[a], 16);
-    gd[a] += __shfl_xor(gd[a], 32);
-    gd[a] *= unscale;
+    gx[a] = group_sum(gx[a]) * (f.inv_ext[a] * unscale);  // d pos / d p = N_l / extent (N_l applied above)
+    if (DIR) gd[a] = group_sum(gd[a]) * unscale;
   }
 }
 
 // The backward kernel of the separate-kernel path: one 16-sample column tile
 // per wavefront, reading d loss / d h_0 and d loss / d z from the composite
-// kernel, and storing each sample's torque and force terms for the
-// reduction.  DIR: the SH direction path (sh_dir_grad) is on; without it the
+// kernel, and storing each sample's force for the reduction.  Beside the vector
+// work, the texture unit bounds it (16 cycles for every load or store
+// instruction of a wavefront, 4 wavefronts' tiles per CU at a time): a tile
+// takes 6 loads and 1 store (18 and 3 with one load per incoming value, mask
+// word, ray and level resolution, and torques stored beside forces).  Lane-group
+// exchanges are register swaps, not LDS reads, for the LDS is the busiest unit
+// here too (49 reads per tile).  39.5 M samples of 16 levels: 3.08 ms, 3.25 ms
+// before.  DIR: the SH direction path (sh_dir_grad) is on; without it the
 // SH rows of colour layer 1 are not staged, and four blocks fit a CU's LDS.
 template <int LPG, bool DIR, bool H>
 __global__ __launch_bounds__(kBlock) void k_mlp_bwd(DevField f, DevBatch b, DevWork w) {
@@ -600,9 +658,11 @@ __global__ __launch_bounds__(kBlock) void k_mlp_bwd(DevField f, DevBatch b, DevW
   using A = Arith<H>;
   constexpr int NU = DIR ? kBwdUnits : kBSH;  // staged weight units
   __shared__ typename A::Unit lds[NU];
-  __shared__ float s_c3[64 * 3];
+  __shared__ __align__(16) float s_c3[4][16][3];
+  __shared__ __align__(16) float s_res[4][4];
   stage(lds, A::bwd(f), NU, A::kWords);
-  for (int i = threadIdx.x; i < 64 * 3; i += kBlock) s_c3[i] = f.wc3[i];
+  stage_res(f, s_res);
+  stage_c3(f, s_c3);
   __syncthreads();
 
   const int S = *w.total;
@@ -611,43 +671,35 @@ __global__ __launch_bounds__(kBlock) void k_mlp_bwd(DevField f, DevBatch b, DevW
   const int wave = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   const int n_waves = gridDim.x * (kBlock / 64);
   const SplitK sk = split_k(f);
+  const float* const in = g == 0 ? w.sig : g == 1 ? w.cr : g == 2 ? w.cg : w.cb;
 
   for (int tile = wave; tile < n_tiles; tile += n_waves) {
     // the weight units are re-read from LDS every tile: hoisted out of the
     // loop they would pin ~150 registers and cap occupancy at 1 wave/SIMD
     asm volatile("" ::: "memory");
-    const uint32_t* mw = w.masks + (size_t)tile * 2 * 64 + lane;
     // word 0: density layer 1 (base 0) and colour layer 1 (base 8); word 1:
     // colour layer 2 (base 0)
-    const uint32_t mw0 = mw[0], mw1 = mw[64];
+    const uint2 mw = reinterpret_cast<const uint2*>(w.masks)[(size_t)tile * 64 + lane];
     const int s = tile * 16 + col;
     const int sc = s < S ? s : S - 1;
     const bool ok = s < S;
-    const float z[3] = {ok ? w.cr[sc] : 0.0f, ok ? w.cg[sc] : 0.0f, ok ? w.cb[sc] : 0.0f};
-    const float gh0 = ok ? w.sig[sc] : 0.0f;
-    float d[3];
-    sample_dir(w, sc, d);
+    // lane group 0 loads the column's d loss / d h_0, group q + 1 d loss / d z_q
+    const float own = ok ? in[sc] : 0.0f;
+    float z[3], gh0, r02, r13;
+    swap16(own, r02, r13);
+    swap32(r02, gh0, z[1]);
+    swap32(r13, z[0], z[2]);
+    float d[3] = {0.f, 0.f, 0.f};
+    if (DIR) sample_dir(w, sc, d);
     float gx[3], gd[3];
-    bwd_tile<LPG, DIR, H>(f, w, lds, s_c3, sk, lane, z, gh0, mw0, mw1, sc, d, gx, gd);
-    // the sample's terms: force dL/dp, torque d x (t dL/dp + dL/dd)
-    if (ok && g < 2) {
-      const float t = w.t[s];
-      const float m[3] = {t * gx[0] + gd[0], t * gx[1] + gd[1], t * gx[2] + gd[2]};
-      // lane group 0 stores the torque, group 1 the force
-      float o0, o1, o2;
-      if (g == 0) {
-        o0 = d[1] * m[2] - d[2] * m[1];
-        o1 = d[2] * m[0] - d[0] * m[2];
-        o2 = d[0] * m[1] - d[1] * m[0];
-      } else {
-        o0 = gx[0];
-        o1 = gx[1];
-        o2 = gx[2];
-      }
-      float* out = w.feat + (int64_t)(3 * g) * w.cap;  // feature rows are free by now
-      out[s] = o0;
-      out[w.cap + s] = o1;
-      out[2 * w.cap + s] = o2;
+    bwd_tile<LPG, DIR, H>(f, w, lds, s_c3, sk, s_res, lane, z, gh0, mw.x, mw.y, sc, d, gx, gd);
+    // the sample's force dL/dp in rows 0..2 of the feature array (free by now)
+    // and on the direction path dL/dd in rows 3..5, component g by lane group g
+    // (the reduction forms the torque d x (t dL/dp + dL/dd) from them)
+    if (ok && g < 3) {
+      float* out = w.feat + (int64_t)g * w.cap;
+      out[s] = g == 0 ? gx[0] : g == 1 ? gx[1] : gx[2];
+      if (DIR) out[3 * w.cap + s] = g == 0 ? gd[0] : g == 1 ? gd[1] : gd[2];
     }
   }
 }
@@ -670,9 +722,11 @@ __global__ __launch_bounds__(kBlock) void k_ray_bwd(DevField f, DevBatch b, DevW
   using A = Arith<H>;
   constexpr int NU = DIR ? kBwdUnits : kBSH;
   __shared__ typename A::Unit lds[NU];
-  __shared__ float s_c3[64 * 3];
+  __shared__ __align__(16) float s_c3[4][16][3];
+  __shared__ __align__(16) float s_res[4][4];
   stage(lds, A::bwd(f), NU, A::kWords);
-  for (int i = threadIdx.x; i < 64 * 3; i += kBlock) s_c3[i] = f.wc3[i];
+  stage_res(f, s_res);
+  stage_c3(f, s_c3);
   __syncthreads();
 
   const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
@@ -762,9 +816,9 @@ __global__ __launch_bounds__(kBlock) void k_ray_bwd(DevField f, DevBatch b, DevW
         const float gh = __shfl(gh0, src);
         // the sample's mask words, where the forward kernel's column tile of
         // 16 compacted samples left them for this lane group
-        const uint32_t* mw = w.masks + (size_t)(s >> 4) * 2 * 64 + 16 * g + (s & 15);
+        const uint2 mw = reinterpret_cast<const uint2*>(w.masks)[(size_t)(s >> 4) * 64 + 16 * g + (s & 15)];
         float gx[3], gd[3];
-        bwd_tile<LPG, DIR, H>(f, w, lds, s_c3, sk, lane, z, gh, mw[0], mw[64], s, d, gx, gd);
+        bwd_tile<LPG, DIR, H>(f, w, lds, s_c3, sk, s_res, lane, z, gh, mw.x, mw.y, s, d, gx, gd);
         const float t = w.t[s];
         if (ok) {
 #pragma unroll
@@ -773,14 +827,10 @@ __global__ __launch_bounds__(kBlock) void k_ray_bwd(DevField f, DevBatch b, DevW
             G[a] += gx[a];
           }
         }
-        if (KEEP && ok && g < 2) {
-          const float m[3] = {t * gx[0] + gd[0], t * gx[1] + gd[1], t * gx[2] + gd[2]};
-          const float o[3] = {g == 0 ? d[1] * m[2] - d[2] * m[1] : gx[0],
-                              g == 0 ? d[2] * m[0] - d[0] * m[2] : gx[1],
-                              g == 0 ? d[0] * m[1] - d[1] * m[0] : gx[2]};
-          float* out = w.feat + (int64_t)(3 * g) * w.cap;
-#pragma unroll
-          for (int a = 0; a < 3; ++a) out[a * w.cap + s] = o[a];
+        if (KEEP && ok && g < 3) {  // as k_mlp_bwd stores them
+          float* out = w.feat + (int64_t)g * w.cap;
+          out[s] = g == 0 ? gx[0] : g == 1 ? gx[1] : gx[2];
+          if (DIR) out[3 * w.cap + s] = g == 0 ? gd[0] : g == 1 ? gd[1] : gd[2];
         }
       }
     }

@@ -194,8 +194,9 @@ struct DevWork {
   int32_t* sray;                // ray of each sample
   float* sig;                   // sigma (forward) -> d loss / d h0 (after composite)
   float *cr, *cg, *cb;          // colour (forward) -> d loss / d z (after composite)
-  uint32_t* masks;              // [column tiles of 16][2][64] ReLU masks
-  float* feat;                  // [2L][cap] features; after the backward rows 0..5 = torque, force
+  uint32_t* masks;              // [column tiles of 16][64][2] ReLU masks
+  float* feat;                  // [column tiles of 16][levels, by lane group][16][2] features (see
+                                // encode.hip); after the backward [6][cap]: force, dL/dd
   __half* jac;                  // [6L][cap] d feature / d pos: 12-byte records per sample and
                                 // level in 32-sample blocks (jac_record in encode.hip)
   int64_t cap;                  // sample capacity (row stride of feat and jac)
