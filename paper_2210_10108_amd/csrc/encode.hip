@@ -23,7 +23,7 @@
 // What bounds it: 4 lines per sample and hashed level at the L1's misses in
 // flight times the L2's latency, then the texture unit (16 cycles for any
 // gather instruction, 32 for a 16-byte load) and the vector work beside it.  On
-// 39.5 M samples (16 levels, 2^19 entries, fp32) the kernel takes 7.9 ms
+// 39.5 M samples (16 levels, 2^19 entries, fp32) the kernel takes 7.7 ms
 // against 8.6 ms with per-lane ray lookups, positions recovered in float and a
 // queue per dense level; with every gather in L1 it took 5.0 ms, without
 // gathers 4.2 ms.
