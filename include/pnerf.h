@@ -315,7 +315,10 @@ pnerf_status pnerf_march(pnerf_field* field, int32_t K, const float* poses, int3
  *           (z = pre-sigmoid colour)
  *   what 3: after pnerf_render_loss_grad (t d x dL/dp, dL/dp) [n][6]
  * PNERF_ERR_INVALID_ARG if n exceeds the workspace, `what` is unknown, or
- * `what` > 0 after a pnerf_render_loss_grad with backward = 1. */
+ * `what` > 0 after a pnerf_render_loss_grad with backward = 1.  A call that
+ * failed leaves the values of the last successful one where it had not begun to
+ * write that part of the workspace, and PNERF_ERR_INVALID_ARG otherwise (`what`
+ * 3 needs the rays beside the samples, and marching comes first). */
 pnerf_status pnerf_field_inspect(pnerf_field* field, int32_t what, float* dst, int64_t n,
                                  void* stream);
 

@@ -86,7 +86,13 @@ struct pnerf_field {
   int n_slots = 0;              // sample buffers allocated (1 or 2)
   int overlap_chunks = 0;       // chunks a loss-gradient batch is cut into for overlap
   int backward = 0;             // pnerf_field_params::backward
-  bool last_keeps_samples = false;  // the last call left per-sample intermediates
+  // What pnerf_field_inspect may read of the last call that returned PNERF_OK.
+  // A call clears last_rays before it touches the ray workspace and last_chunks
+  // before it touches the sample buffers or the totals, and sets them again only
+  // when it succeeds.
+  int last_chunks = 0;          // its sample chunks (0: its samples are gone)
+  bool last_rays = false;       // the ray records are still its own
+  bool last_keeps_samples = false;  // it left per-sample intermediates
   // internal streams of the pipelined loss gradient: encoding | networks
   hipStream_t s_enc = nullptr, s_mlp = nullptr;
   hipEvent_t ev_start = nullptr, ev_enc[2] = {nullptr, nullptr}, ev_mlp[2] = {nullptr, nullptr};
@@ -96,7 +102,6 @@ struct pnerf_field {
   int max_chunks = 0;
   int32_t* h_hyp = nullptr;     // pinned host copy of the per-hypothesis sample counts
   int h_hyp_cap = 0;
-  int last_chunks = 0;
   int64_t last_total = 0;
   const int32_t* last_total_dev = nullptr;  // the last call's total, when only the device holds it
   int64_t budget = 0;
@@ -406,6 +411,7 @@ pnerf_status ensure_rays(pnerf_field* F, int n_rays, int n_hyp, hipStream_t s, b
     if (st != PNERF_OK) return st;
   }
   if (n_rays > F->rays_cap || n_hyp > F->rays_hyp) {
+    F->last_rays = false;
     n_rays = std::max(n_rays, F->rays_cap);
     n_hyp = std::max(n_hyp, F->rays_hyp);
     if (F->d_rays) {
@@ -445,6 +451,7 @@ pnerf_status ensure_samples(pnerf_field* F, int64_t need, int64_t limit, int n_c
     if (st != PNERF_OK) return st;
   }
   if (n_chunks > F->max_chunks) {
+    F->last_chunks = 0;
     if (F->d_totals) {
       HIP_TRY(hipStreamSynchronize(s));
       HIP_TRY(hipFree(F->d_totals));
@@ -460,6 +467,7 @@ pnerf_status ensure_samples(pnerf_field* F, int64_t need, int64_t limit, int n_c
                                      : std::max(need, std::min(limit, F->samp_cap + F->samp_cap / 4));
   cap = (cap + kTile - 1) / kTile * kTile;
   slots = std::max(slots, F->n_slots);
+  F->last_chunks = 0;
   HIP_TRY(hipStreamSynchronize(s));
   for (int q = 0; q < 2; ++q) {
     if (F->d_samp[q]) HIP_TRY(hipFree(F->d_samp[q]));
@@ -594,7 +602,6 @@ pnerf_status run(pnerf_field* F, Mode mode, int32_t K, const float* poses, int32
     return fail(PNERF_ERR_NOT_SUPPORTED, "only render_loss_grad, without profiling, can be "
                                          "recorded under stream capture");
   F->last_total_dev = nullptr;
-  F->last_keeps_samples = mode != kLossGrad || F->backward != 1;
   const int64_t max_rays = (int64_t)kMaxScanBlocks * 256;
   int32_t kr = 0;
   pnerf_status st = pnerf_plan_counted_batch(K, P, F->dev.max_per_ray, &kr);
@@ -636,6 +643,7 @@ pnerf_status run(pnerf_field* F, Mode mode, int32_t K, const float* poses, int32
     if (st != PNERF_OK) return st;
     DevWork wb = counted_work(F);
     int raw_blocks = 0;  // device-sized: the write pass may finish the offset scan itself
+    F->last_rays = false;
     HIP_TRY(timed(F, "march", s, [&] {
       return launch_march_count(F->dev, bb, wb, device_sized, &raw_blocks, s);
     }));
@@ -687,6 +695,7 @@ pnerf_status run(pnerf_field* F, Mode mode, int32_t K, const float* poses, int32
       if (overlap) HIP_TRY(hipStreamWaitEvent(se, F->ev_mlp[slot], 0));
       // inspection: lattice indices go to the (otherwise unused) blue-channel buffer
       int32_t* j_tmp = mode == kMarch ? reinterpret_cast<int32_t*>(w.cb) : nullptr;
+      F->last_chunks = 0;
       HIP_TRY(timed(F, "march_write", se, [&] {
         return launch_march_write(F->dev, b, wb, w, a * P, (int)base, (int)sums[c], raw_blocks, j_tmp,
                                   se);
@@ -747,6 +756,8 @@ pnerf_status run(pnerf_field* F, Mode mode, int32_t K, const float* poses, int32
     F->last_total_dev = device_sized ? wb.total : nullptr;
   }
   F->last_chunks = chunk_id;
+  F->last_rays = true;
+  F->last_keeps_samples = mode != kLossGrad || F->backward != 1;
   F->last_total = grand;
   return PNERF_OK;
 }
@@ -1167,10 +1178,16 @@ pnerf_status pnerf_field_inspect(pnerf_field* F, int32_t what, float* dst, int64
   if (!F || !dst) return fail(PNERF_ERR_INVALID_ARG, "NULL argument");
   if (what < 0 || what > 3) return fail(PNERF_ERR_INVALID_ARG, "what=%d", what);
   if (!F->d_samp[0] || n < 0 || n > F->samp_cap) return fail(PNERF_ERR_INVALID_ARG, "n=%lld", (long long)n);
+  if (F->last_chunks == 0)
+    return fail(PNERF_ERR_INVALID_ARG, "no samples: a later call failed after it had begun to "
+                                       "write the sample workspace");
   if (F->last_chunks != 1) return fail(PNERF_ERR_INVALID_ARG, "last call used %d chunks", F->last_chunks);
   if (what > 0 && !F->last_keeps_samples)
     return fail(PNERF_ERR_INVALID_ARG,
                 "the last loss gradient kept no per-sample intermediates (backward = 1)");
+  if (what == 3 && !F->last_rays)  // the torque is formed from the ray records
+    return fail(PNERF_ERR_INVALID_ARG, "the rays are gone: a later call failed after it had begun "
+                                       "to write the ray workspace");
   const DevWork w = chunk_work(F, 0, 0, 0);  // the single chunk of the last call
   HIP_TRY(launch_inspect(F->dev, DevBatch{}, w, what, dst, n, (hipStream_t)stream));
   return PNERF_OK;

@@ -291,6 +291,30 @@ def test_inspect_needs_a_backward_that_keeps_samples(pn):
     f.close()
 
 
+def test_inspect_after_a_refused_call(pn):
+    # the refused call has marched its own rays: the samples of the call before
+    # are still there, the rays that their torque is formed from are not
+    case = G.make_case("tiny32", K=1, P=1024)
+    few = np.ascontiguousarray(case.pix[:, :128])
+    obs = G.to_dev(np.random.default_rng(0).uniform(0, 1, (32, 32, 3)).astype(np.float32))
+    poses = G.to_dev(case.poses)
+    f = pn.Field(case.spec, max_workspace_bytes=1 << 20)
+    f.render_loss_grad(poses, G.to_dev(few), obs, case.intr)
+    n = f.last_sample_count()
+    before = [f.inspect(what, n).cpu().numpy() for what in range(4)]
+    with pytest.raises(pn.PnerfError) as e:
+        f.render_loss_grad(poses, G.to_dev(case.pix), obs, case.intr)
+    assert e.value.status == pn.ERR_CAPACITY
+    with pytest.raises(pn.PnerfError) as e:
+        f.inspect(3, n)
+    assert e.value.status == pn.ERR_INVALID_ARG
+    for what in range(3):
+        assert np.array_equal(f.inspect(what, n).cpu().numpy(), before[what])
+    f.render_loss_grad(poses, G.to_dev(few), obs, case.intr)
+    assert np.array_equal(f.inspect(3, n).cpu().numpy(), before[3]) and np.any(before[3])
+    f.close()
+
+
 @pytest.mark.parametrize("seed", [1, 2, 3, 4])
 @pytest.mark.parametrize("lattice", [False, True])
 def test_loss_grad_other_seeds(pn, seed, lattice):

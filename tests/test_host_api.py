@@ -1,0 +1,122 @@
+"""The library's host code with a stand-in for the device (host_api/): what a
+call that fails half way leaves for the inspection, on the CPU."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2210_10108_amd import build, pnerf, synth
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+pytestmark = pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="hipcc not installed")
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host_api")
+    objs = []
+    for src in (os.path.join(build.CSRC, "api.hip"), os.path.join(HERE, "host_api", "fake_device.cpp")):
+        objs.append(str(d / (os.path.basename(src) + ".o")))
+        subprocess.run([build.HIPCC, "-x", "hip", "--offload-host-only", "-O1", "-g", "-std=c++17",
+                        "-fPIC", "-I", os.path.join(build.HERE, "..", "include"), "-c", src, "-o",
+                        objs[-1]], check=True, capture_output=True)
+    so = str(d / "libpnerf_host.so")
+    subprocess.run(["g++", "-shared", "-fPIC", *objs, "-o", so], check=True)
+    L = C.CDLL(so)
+    for name, (res, args) in pnerf._SIGS.items():
+        getattr(L, name).restype = res
+        getattr(L, name).argtypes = args
+    L.fake_bytes.restype = L.fake_peak.restype = C.c_size_t
+    L.fake_limit.argtypes = [C.c_size_t]
+    return L
+
+
+class HostField:
+    """A field of the stand-in library; calls return the status."""
+
+    def __init__(self, L, log2_table=10, n_levels=4, param_dtype="f32", n_uniform=4096, **kw):
+        L.fake_reset()
+        self.L = L
+        npdt = np.float32 if param_dtype == "f32" else np.float16
+        zeros = lambda *s: np.zeros(s, npdt)  # noqa: E731
+        p = self.p = pnerf.FieldParams()
+        self.keep = [synth.level_resolutions(n_levels, 16, 2048).astype(np.int32),
+                     zeros(n_levels, 1 << log2_table, 2), zeros(2 * n_levels, 64), zeros(64, 16),
+                     zeros(32, 64), zeros(64, 64), zeros(64, 3)]
+        names = ["level_res", "table", "w_density1", "w_density2", "w_color1", "w_color2", "w_color3"]
+        for n, a in zip(names, self.keep):
+            setattr(p, n, a.ctypes.data_as(C.c_void_p))
+        p.n_levels, p.n_features, p.log2_table_size = n_levels, 2, log2_table
+        p.param_dtype, p.dense_coarse_levels = int(param_dtype == "f16"), 1
+        p.aabb_min, p.aabb_max = (C.c_float * 3)(-.5, -.5, -.5), (C.c_float * 3)(.5, .5, .5)
+        p.n_uniform, p.loss_param = n_uniform, 0.01
+        for k, v in kw.items():
+            setattr(p, k, v)
+        self.base = L.fake_bytes()
+        self.h = C.c_void_p()
+        assert L.pnerf_create_field(C.byref(p), None, C.byref(self.h)) == pnerf.OK
+        self.own = L.fake_bytes() - self.base  # tables and weights
+
+    def close(self):
+        self.L.pnerf_destroy_field(self.h)
+        assert self.L.fake_bytes() == self.base
+
+    def loss_grad(self, K, P, samples):
+        self.L.fake_samples(samples)
+        dev = np.zeros(4, np.float32).ctypes.data_as(C.c_void_p)  # never read
+        it = pnerf.Intrinsics(32, 32, 40.0, 40.0, 16.0, 16.0)
+        return self.L.pnerf_render_loss_grad(self.h, K, dev, P, dev, dev, C.byref(it), dev, dev, None)
+
+    def inspect(self, what):
+        """(status, call the samples are from, call the ray records are from)"""
+        dst = np.zeros(64, np.float32)
+        st = self.L.pnerf_field_inspect(self.h, what, dst.ctypes.data_as(C.c_void_p), 1, None)
+        return st, int(dst[0]), int(dst[1])
+
+
+# Sizes for which the call reads its sample totals (its worst case, 4096 samples
+# a ray, is above what one buffer may be sized for on the device)
+HOST_PLANNED = dict(K=2, P=65536)
+
+
+def test_inspect_after_a_call_that_does_not_fit_the_workspace(lib):
+    # the failed call has marched, so the ray records are its own: the torque of
+    # a sample of the call before cannot be formed from them any more
+    f = HostField(lib, max_workspace_bytes=200 << 20)
+    assert f.loss_grad(samples=1000, **HOST_PLANNED) == pnerf.OK
+    assert f.inspect(3) == (pnerf.OK, 1, 1)
+    assert f.loss_grad(samples=50_000_000, **HOST_PLANNED) == pnerf.ERR_CAPACITY
+    assert f.inspect(3)[0] == pnerf.ERR_INVALID_ARG
+    for what in (0, 1, 2):  # the sample buffer is still that of the first call
+        assert f.inspect(what)[:2] == (pnerf.OK, 1)
+    assert f.loss_grad(samples=2000, **HOST_PLANNED) == pnerf.OK
+    assert f.inspect(3) == (pnerf.OK, 3, 3)
+    f.close()
+
+
+def test_inspect_after_the_ray_workspace_could_not_grow(lib):
+    f = HostField(lib)
+    assert f.loss_grad(samples=1000, **HOST_PLANNED) == pnerf.OK
+    lib.fake_limit(lib.fake_bytes())
+    assert f.loss_grad(K=4, P=65536, samples=1000) == pnerf.ERR_OUT_OF_MEMORY
+    n = lib.fake_inspected()
+    assert f.inspect(3)[0] == pnerf.ERR_INVALID_ARG
+    assert lib.fake_inspected() == n  # no kernel on records that are not there
+    assert f.inspect(0)[:2] == (pnerf.OK, 1)
+    lib.fake_limit((1 << 64) - 1)
+    assert f.loss_grad(K=4, P=65536, samples=1000) == pnerf.OK
+    assert f.inspect(3) == (pnerf.OK, 2, 2)
+    f.close()
+
+
+def test_inspect_after_the_sample_workspace_could_not_grow(lib):
+    f = HostField(lib)
+    assert f.loss_grad(samples=1000, **HOST_PLANNED) == pnerf.OK
+    lib.fake_limit(lib.fake_bytes())
+    assert f.loss_grad(samples=5_000_000, **HOST_PLANNED) == pnerf.ERR_OUT_OF_MEMORY
+    for what in range(4):
+        assert f.inspect(what)[0] == pnerf.ERR_INVALID_ARG
+    f.close()
