@@ -293,15 +293,17 @@ struct Carver {
   }
 };
 
-// Per-ray arrays for n_rays rays (one counted batch).  `offc` receives the
-// sample chunks' own exclusive offsets.
+// Per-ray arrays for n_rays rays (one counted batch).  Chunks are disjoint ranges
+// of its rays and hypotheses, so that chunks in flight together share these
+// arrays, each its own range; only a chunk's own exclusive offsets, one more than
+// its rays, are kept per sample buffer.
 struct RayWs {
   float4* rrec;
   float *rtn, *rtf, *rdelta, *rsh;
   int32_t *count, *off, *blocksum, *hyp_total;
-  int32_t* offc[2];             // per sample buffer: the chunk's own offsets,
-  float *ray_loss[2], *partial[2];  // per-ray losses and reduction partials
-  float* ray_terms[2];          // fused backward: [n_rays][7] per-ray torque, force, loss
+  int32_t* offc[2];             // per sample buffer: the chunk's own offsets
+  float *ray_loss, *partial;    // per-ray losses and [n_hyp][kReduceParts][7] reduction partials
+  float* ray_terms;             // fused backward: [n_rays][7] per-ray torque, force, loss
 };
 
 size_t carve_rays(int n_rays, int n_hyp, RayWs* r, char* base) {
@@ -318,22 +320,11 @@ size_t carve_rays(int n_rays, int n_hyp, RayWs* r, char* base) {
   x.off = c.take<int32_t>(R + 1);
   x.blocksum = c.take<int32_t>((R + 255) / 256);
   x.hyp_total = c.take<int32_t>(R);
-  for (int q = 0; q < 2; ++q) {
-    x.offc[q] = c.take<int32_t>(R + 1);
-    x.ray_loss[q] = c.take<float>(R);
-    x.partial[q] = c.take<float>((size_t)n_hyp * kReduceParts * 7);
-    x.ray_terms[q] = c.take<float>(R * 7);
-  }
+  for (int q = 0; q < 2; ++q) x.offc[q] = c.take<int32_t>(R + 1);
+  x.ray_loss = c.take<float>(R);
+  x.partial = c.take<float>((size_t)n_hyp * kReduceParts * 7);
+  x.ray_terms = c.take<float>(R * 7);
   return c.off;
-}
-
-// What the workspace budget sets aside for the rays: fixed sizes per ray and
-// hypothesis, so that a budget cuts a batch into the same chunks whichever
-// per-ray arrays the kernels keep (carve_rays takes 24 bytes a ray more).
-int64_t budget_rays(int64_t R, int64_t n_hyp) {
-  const auto words = [](int64_t n) { return (int64_t)align_up((size_t)n * 4); };
-  return 11 * words(R) + words(16 * R) + words(R + 1) + words((R + 255) / 256) +
-         2 * (words(R + 1) + words(R) + words(n_hyp * kReduceParts * 7) + words(7 * R));
 }
 
 // Per-sample arrays for cap samples (one chunk); cap is a multiple of kTile.
@@ -372,7 +363,7 @@ DevWork counted_work(pnerf_field* F) {
   return w;
 }
 
-DevWork chunk_work(pnerf_field* F, int ray_base, int chunk_id, int slot) {
+DevWork chunk_work(pnerf_field* F, int ray_base, int hyp_base, int chunk_id, int slot) {
   RayWs r{};
   carve_rays(F->rays_cap, F->rays_hyp, &r, (char*)F->d_rays);
   DevWork w{};
@@ -384,9 +375,9 @@ DevWork chunk_work(pnerf_field* F, int ray_base, int chunk_id, int slot) {
   w.off = r.offc[slot];
   w.blocksum = nullptr;
   w.hyp_total = nullptr;
-  w.ray_loss = r.ray_loss[slot];
-  w.partial = r.partial[slot];
-  w.ray_terms = r.ray_terms[slot];
+  w.ray_loss = r.ray_loss + ray_base;
+  w.partial = r.partial + (size_t)kReduceParts * 7 * hyp_base;
+  w.ray_terms = r.ray_terms + (size_t)7 * ray_base;
   w.total = F->d_totals + chunk_id;
   w.queue = F->d_queue;
   return w;
@@ -611,8 +602,9 @@ pnerf_status run(pnerf_field* F, Mode mode, int32_t K, const float* poses, int32
   st = ensure_rays(F, kr * P, kr, s, capturing);
   if (st != PNERF_OK) return st;
   const int64_t per_sample = bytes_per_sample(F->dev);  // per buffer
+  const int64_t ray_bytes = (int64_t)carve_rays(F->rays_cap, F->rays_hyp, nullptr, nullptr);
   const int64_t limit = std::min<int64_t>(
-      std::max<int64_t>((F->budget - budget_rays(F->rays_cap, F->rays_hyp)) / per_sample, kTile),
+      std::max<int64_t>((F->budget - ray_bytes) / per_sample, kTile),
       ((int64_t)1 << 31) - 4 * kTile);
   // loss gradient: several chunks, encoding of one overlapping the networks of
   // the previous, on two internal streams with a sample buffer each
@@ -690,7 +682,7 @@ pnerf_status run(pnerf_field* F, Mode mode, int32_t K, const float* poses, int32
       const int a = cut[c], kn = cut[c + 1] - cut[c], k0 = h0 + a;
       const int slot = overlap ? c & 1 : 0;
       DevBatch b = make_batch(kn, poses + (size_t)12 * k0, P, pix + (size_t)P * k0, obs, intr);
-      DevWork w = chunk_work(F, a * P, chunk_id, slot);
+      DevWork w = chunk_work(F, a * P, a, chunk_id, slot);
       // the buffer is free once the networks of chunk c - 2 are done
       if (overlap) HIP_TRY(hipStreamWaitEvent(se, F->ev_mlp[slot], 0));
       // inspection: lattice indices go to the (otherwise unused) blue-channel buffer
@@ -1188,7 +1180,7 @@ pnerf_status pnerf_field_inspect(pnerf_field* F, int32_t what, float* dst, int64
   if (what == 3 && !F->last_rays)  // the torque is formed from the ray records
     return fail(PNERF_ERR_INVALID_ARG, "the rays are gone: a later call failed after it had begun "
                                        "to write the ray workspace");
-  const DevWork w = chunk_work(F, 0, 0, 0);  // the single chunk of the last call
+  const DevWork w = chunk_work(F, 0, 0, 0, 0);  // the single chunk of the last call
   HIP_TRY(launch_inspect(F->dev, DevBatch{}, w, what, dst, n, (hipStream_t)stream));
   return PNERF_OK;
 }

@@ -120,3 +120,43 @@ def test_inspect_after_the_sample_workspace_could_not_grow(lib):
     for what in range(4):
         assert f.inspect(what)[0] == pnerf.ERR_INVALID_ARG
     f.close()
+
+
+# Bytes of a workspace beyond the budget that are not an overrun: the last tile
+# of 64 samples in each buffer, and the totals of up to 16 chunks
+def allowance(n_levels, buffers):
+    return buffers * 64 * (56 + 20 * n_levels) + 4 * 17
+
+
+@pytest.mark.parametrize("overlap", [1, 4])
+@pytest.mark.parametrize("n_levels", [4, 16])
+@pytest.mark.parametrize("budget,K,P", [(1 << 20, 8, 200), (1 << 20, 16, 96), (64 << 20, 16, 4096),
+                                        (1 << 30, 8, 1 << 18)])
+def test_the_workspace_stays_within_its_budget(lib, budget, K, P, n_levels, overlap):
+    # hypotheses of about half a sample buffer each, among them those of which
+    # two just fill it
+    buffers = 1 + (overlap > 1 and budget > 1 << 20)  # small batches do not overlap
+    cap = (budget - 176 * K * P - 1800 * K) / (56 + 20 * n_levels) / buffers
+    most = 0
+    for part in np.linspace(0.45, 0.55, 60):
+        f = HostField(lib, n_levels=n_levels, max_workspace_bytes=budget, overlap_chunks=overlap,
+                      n_uniform=1000)
+        start = lib.fake_bytes()
+        assert f.loss_grad(K=K, P=P, samples=int(part * cap)) == pnerf.OK
+        assert lib.fake_encodes() > 1
+        most = max(most, lib.fake_peak() - start)
+        f.close()
+    assert 0.96 * budget < most <= budget + allowance(n_levels, buffers)
+
+
+def test_a_batch_takes_as_few_chunks_as_with_smaller_rays(lib):
+    # what a ray takes of the budget: no more than 184 bytes, and a hypothesis no
+    # more than 3584, as when the rays were kept in separate arrays; a batch that
+    # fills the budget beside them still runs as one chunk
+    budget, K, P, L = 64 << 20, 16, 4096, 8
+    per_sample = 56 + 20 * L
+    f = HostField(lib, n_levels=L, max_workspace_bytes=budget)
+    samples = (budget - 184 * K * P - 3584 * K - 20 * 256) // (per_sample + 1) // K
+    assert f.loss_grad(K=K, P=P, samples=samples) == pnerf.OK
+    assert lib.fake_encodes() == 1
+    f.close()
