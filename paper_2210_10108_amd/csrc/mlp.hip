@@ -272,6 +272,7 @@ __device__ __forceinline__ void sample_dir(const DevWork& w, int s, float d[3]) 
 // Mask bits of a ReLU layer's 16 values t[m][i] of one column tile (unit
 // 16m + 4g + i): value v = 4m + i is K position v % 8 of K step v / 8, so its
 // bit is base + 4 (v / 8) + (v % 8) / 2, plus 16 for odd v (see relu_pack2).
+template <bool RAY>
 __device__ __forceinline__ void apply_mask(floatx4 (&t)[4], uint32_t mk, int base) {
 #pragma unroll
   for (int m = 0; m < 4; ++m)
@@ -279,6 +280,10 @@ __device__ __forceinline__ void apply_mask(floatx4 (&t)[4], uint32_t mk, int bas
     for (int i = 0; i < 4; ++i) {
       const int v = 4 * m + i;
       const int bit = base + 4 * (v / 8) + (v % 8) / 2 + 16 * (v & 1);
+      if (RAY) {  // the compiler's own choice of instructions (see bwd_tile)
+        if (!((mk >> bit) & 1u)) t[m][i] = 0.0f;
+        continue;
+      }
       // the bit spread over a word (one bit-field extract), and one AND
       int on;
       asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(on) : "v"(mk), "n"(bit));
@@ -301,8 +306,13 @@ __device__ __forceinline__ void swap32(float x, float& lo, float& hi) {
 }
 
 // Sum of the four lane groups' values, in every group (as adding the values of
-// lanes l ^ 16, then l ^ 32).
+// lanes l ^ 16, then l ^ 32).  RAY: see bwd_tile.
+template <bool RAY>
 __device__ __forceinline__ float group_sum(float x) {
+  if (RAY) {
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+  }
   float a, b;
   swap16(x, a, b);
   swap32(a + b, a, b);
@@ -513,11 +523,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // the sample of column col.  In: z = d loss / d z of that sample (zero when it
 // has none), gh0 = d loss / d h_0 of that sample (in every lane group), the
 // sample's two ReLU mask words as the forward kernel stored them for this lane
-// group, s_res = the staged resolutions N_l (stage_res), and sc = the sample whose Jacobian records are read (any valid sample
-// when the column is empty).  Out: d loss / d p of the sample, gx (in every
-// lane group, after the sums over the groups), and on the direction path the
-// term d loss / d d through the SH input, gd (likewise summed).
-template <int LPG, bool DIR, bool H>
+// group, s_res = the staged resolutions N_l (stage_res), and sc = the sample
+// whose Jacobian records are read (any valid sample when the column is empty).
+// Out: d loss / d p of the sample, gx (in every lane group, after the sums over
+// the groups), and on the direction path the term d loss / d d through the SH
+// input, gd (likewise summed).
+//
+// RAY: called by k_ray_bwd, of which 2 blocks fit a CU (k_mlp_bwd: 4), so that
+// its waits are hardly covered by other wavefronts.  There the Jacobian records
+// are loaded before the networks instead of where they are used, and masks and
+// lane-group sums are left to instructions that the compiler can schedule, with
+// which every variant of k_ray_bwd keeps to 128 registers (the direction path
+// took 130 to 138, and one block per CU).  k_ray_bwd on 5.4 M samples of 16
+// levels, with and without the three: 611 and 685 us, on the direction path 680
+// and 997, fp16 networks 510 and 611, on the direction path 567 and 657.
+template <int LPG, bool DIR, bool H, bool RAY = false>
 __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
                                          const typename Arith<H>::Unit* lds, const float (*s_c3)[16][3],
                                          const SplitK& sk, const float (*s_res)[4], int lane,
@@ -529,6 +549,20 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
   constexpr int MD = (LPG + 1) / 2;  // row tiles of d loss / d feature
   const int g = lane >> 4;
   const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+  // this lane group's Jacobian records of the sample (level 4j + g at record j),
+  // six fp16 values each; read once: non-temporal, so that they do not displace
+  // cached data
+  auto load_record = [&](int j, uint32_t r[3]) {
+    const uint32_t* jp = reinterpret_cast<const uint32_t*>(w.jac) +
+                         (((int64_t)(sc >> 5) * 4 + g) * (6 * LPG * 32) + (sc & 31) * 6) / 2;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r[k] = __builtin_nontemporal_load(jp + j * (32 * 6 / 2) + k);
+  };
+  uint32_t early[LPG][3];
+  if (RAY) {
+#pragma unroll
+    for (int j = 0; j < LPG; ++j) load_record(j, early[j]);
+  }
   // fp16 operands: the sample's gradient scaled by 2^k, its largest component
   // (biased exponent ex) into [16, 32); k is kept within +-100
   float scale = 1.0f, unscale = 1.0f;
@@ -551,7 +585,7 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
       const float* c3 = s_c3[g][4 * m + i];
       gb2[m][i] = c3[0] * z[0] + c3[1] * z[1] + c3[2] * z[2];
     }
-  apply_mask(gb2, mw1, 0);
+  apply_mask<RAY>(gb2, mw1, 0);
   // colour layer 2 transposed
   floatx4 gb1[4] = {zero, zero, zero, zero};
 #pragma unroll
@@ -562,7 +596,7 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
 #pragma unroll
     for (int m = 0; m < 4; ++m) gb1[m] = A::mma(A::load(lds, kBC2 + 2 * m + s2, lane), x, gb1[m]);
   }
-  apply_mask(gb1, mw0, 8);
+  apply_mask<RAY>(gb1, mw0, 8);
   // colour layer 1 transposed: rows = h index (row 0 has zero weights); SH rows
   floatx4 gh = zero, gsh = zero;
 #pragma unroll
@@ -582,7 +616,7 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
 #pragma unroll
     for (int m = 0; m < 4; ++m) ga[m] = A::mma(A::load(lds, kBD2 + m, lane), x, zero);
   }
-  apply_mask(ga, mw0, 0);
+  apply_mask<RAY>(ga, mw0, 0);
   // density layer 1 transposed: row 4g + i of tile mm = feature i % 2 of
   // level 4 (2 mm + i / 2) + g, so lane group g gets its own levels
   floatx4 gf[MD];
@@ -598,21 +632,16 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
       gf[mm] = A::mma(A::load(lds, kBD1 + 2 * mm + s2, lane), x, gf[mm]);
   }
   // d loss / d p = sum over the lane group's levels 4j + g of d loss / d
-  // feature times the stored Jacobian, then over the 4 groups.  This lane
-  // group's Jacobian records of the sample (level 4j + g at record j), six
-  // fp16 values each
-  const uint32_t* jp = reinterpret_cast<const uint32_t*>(w.jac) +
-                       (((int64_t)(sc >> 5) * 4 + g) * (6 * LPG * 32) + (sc & 31) * 6) / 2;
+  // feature times the stored Jacobian, then over the 4 groups
   gx[0] = gx[1] = gx[2] = 0.f;
   const float4 r4 = *reinterpret_cast<const float4*>(s_res[g]);
   const float res[4] = {r4.x, r4.y, r4.z, r4.w};
 #pragma unroll
   for (int j = 0; j < LPG; ++j) {
     // level 4j + g: d loss / d pos_l = sum_q gf * J, then times N_l
-    const uint32_t* rec = jp + j * (32 * 6 / 2);
-    // read once: non-temporal, so that they do not displace cached data
-    const uint32_t r[3] = {__builtin_nontemporal_load(rec), __builtin_nontemporal_load(rec + 1),
-                           __builtin_nontemporal_load(rec + 2)};
+    uint32_t late[3];
+    if (!RAY) load_record(j, late);
+    const uint32_t* r = RAY ? early[j] : late;
     float J[6];  // d feature_q / d pos_a at 3 q + a; record: (q, a) = (0, 0) (0, 1),
                  // (1, 0) (1, 1), (0, 2) (1, 2)
     constexpr int at[6] = {0, 1, 3, 4, 2, 5};
@@ -636,8 +665,8 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
   }
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    gx[a] = group_sum(gx[a]) * (f.inv_ext[a] * unscale);  // d pos / d p = N_l / extent (N_l applied above)
-    if (DIR) gd[a] = group_sum(gd[a]) * unscale;
+    gx[a] = group_sum<RAY>(gx[a]) * (f.inv_ext[a] * unscale);  // d pos / d p = N_l / extent (N_l applied above)
+    if (DIR) gd[a] = group_sum<RAY>(gd[a]) * unscale;
   }
 }
 
@@ -715,8 +744,8 @@ __global__ __launch_bounds__(kBlock) void k_mlp_bwd(DevField f, DevBatch b, DevW
 // (Eq. 3) is one cross product d x M.  Each ray leaves 7 floats -- torque,
 // force (Eq. 2), loss -- for the per-hypothesis reduction; no per-sample
 // gradient goes to memory.  KEEP also stores every sample's d loss / d h_0,
-// d loss / d z and (torque, force) terms as the separate kernels do
-// (inspection).
+// d loss / d z, force and on the direction path d loss / d d as the separate
+// kernels do (inspection).
 template <int LPG, bool DIR, bool KEEP, bool H>
 __global__ __launch_bounds__(kBlock) void k_ray_bwd(DevField f, DevBatch b, DevWork w) {
   using A = Arith<H>;
@@ -817,9 +846,9 @@ __global__ __launch_bounds__(kBlock) void k_ray_bwd(DevField f, DevBatch b, DevW
         // the sample's mask words, where the forward kernel's column tile of
         // 16 compacted samples left them for this lane group
         const uint2 mw = reinterpret_cast<const uint2*>(w.masks)[(size_t)(s >> 4) * 64 + 16 * g + (s & 15)];
-        float gx[3], gd[3];
-        bwd_tile<LPG, DIR, H>(f, w, lds, s_c3, sk, s_res, lane, z, gh, mw.x, mw.y, s, d, gx, gd);
         const float t = w.t[s];
+        float gx[3], gd[3];
+        bwd_tile<LPG, DIR, H, true>(f, w, lds, s_c3, sk, s_res, lane, z, gh, mw.x, mw.y, s, d, gx, gd);
         if (ok) {
 #pragma unroll
           for (int a = 0; a < 3; ++a) {
@@ -827,10 +856,16 @@ __global__ __launch_bounds__(kBlock) void k_ray_bwd(DevField f, DevBatch b, DevW
             G[a] += gx[a];
           }
         }
-        if (KEEP && ok && g < 3) {  // as k_mlp_bwd stores them
-          float* out = w.feat + (int64_t)g * w.cap;
-          out[s] = g == 0 ? gx[0] : g == 1 ? gx[1] : gx[2];
-          if (DIR) out[3 * w.cap + s] = g == 0 ? gd[0] : g == 1 ? gd[1] : gd[2];
+        if (KEEP) {  // as k_mlp_bwd stores them
+          // from an opaque copy of g, or the compiler keeps the stores' addresses
+          // through the whole tile (129 registers on the direction path)
+          int gs = g;
+          asm volatile("" : "+v"(gs));
+          if (ok && gs < 3) {
+            float* out = w.feat + (int64_t)gs * w.cap;
+            out[s] = gs == 0 ? gx[0] : gs == 1 ? gx[1] : gx[2];
+            if (DIR) out[3 * w.cap + s] = gs == 0 ? gd[0] : gs == 1 ? gd[1] : gd[2];
+          }
         }
       }
     }

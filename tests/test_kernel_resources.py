@@ -16,9 +16,10 @@ BUDGET = {
     "encode.hip": {"k_encodeILb0ELb1E": 7},
     # <levels per lane group, (SH direction path,) (keep,) fp16>
     "mlp.hip": {"k_mlp_fwdILi4ELb1ELb0E": 8, "k_mlp_bwdILi4ELb0ELb0E": 7,
-                "k_mlp_bwdILi4ELb1ELb0E": 6, "k_ray_bwdILi4ELb0ELb0ELb0E": 4,
-                "k_mlp_fwdILi4ELb1ELb1E": 8, "k_mlp_bwdILi4ELb0ELb1E": 8,
-                "k_mlp_bwdILi4ELb1ELb1E": 6},
+                "k_mlp_bwdILi4ELb1ELb0E": 6, "k_mlp_fwdILi4ELb1ELb1E": 8,
+                "k_mlp_bwdILi4ELb0ELb1E": 8, "k_mlp_bwdILi4ELb1ELb1E": 6,
+                # every variant of the fused backward: 2 of its 8-wavefront blocks per CU
+                "k_ray_bwd": 4},
 }
 
 
