@@ -250,28 +250,44 @@ U_t build_bwd_units(const Weights& W, int lpg) {
 // The encoding's work queues: hashed levels first, so that the first queue of
 // every XCD (queue x of XCD x) holds hashed tables, then the dense ones.
 // Consecutive levels of a kind share a queue, and with it each sample's
-// position, while their tables together fit one XCD's L2 (kGroupBytes), or half
-// of it for dense levels (kDenseGroupBytes): more and shorter dense queues fill
-// the XCDs' time beside the hashed ones better.  Encode of 0.8, 14 and 39.5 M
-// samples (16 levels, 2^19 entries, fp32): 220, 2811, 7809 us with 4 MiB of
-// dense tables, 212, 2748, 7678 with 2 MiB, 212, 2754, 7696 with 1 MiB; of 17 M
-// with fp16 tables 4088, 4079, 4148.  Hashed ones at 2 MiB cost 7 % with fp16
-// tables, at 8 MiB 25-38 % with fp32.
+// position:
+//
+// Dense levels while their tables together fit half an XCD's L2
+// (kDenseGroupBytes): more and shorter dense queues fill the XCDs' time beside
+// the hashed ones better.  Encode of 0.8, 14 and 39.5 M samples (16 levels, 2^19
+// entries, fp32): 220, 2811, 7809 us with 4 MiB of dense tables, 212, 2748, 7678
+// with 2 MiB, 212, 2754, 7696 with 1 MiB; of 17 M with fp16 tables 4088, 4079,
+// 4148.
+//
+// Hashed levels while their tables together fit the L2 (kGroupBytes; 8 MiB cost
+// 25-38 % with fp32), but no more than two, or, of small tables, as many as take
+// kSmallGroupBytes together.  A queue's items each run through all its levels:
+// with many levels to a queue a batch has few, long items, which leave the chip
+// idle at its end, and mid-sized tables miss an L1 that holds one of them.
+// Encode of 73 k, 0.44, 2.7 and 10 M samples, 16 levels, fp32: 2^15 entries, 16
+// levels to a queue 66, 183, 504, 1893 us, four 37, 107, 469, 1771, two 30, 100,
+// 479, 1813, one 31, 105, 538, 2030; 2^17 entries, four 44, 139, 549, -, two 32,
+// 109, 487, -; 2^12 entries, 16 levels 38, 95, 352, 1266, four 27, 76, 334, 1224,
+// two 23, 72, 348, 1318; 2^10 entries, 16 levels 34, 79, 288, 1010, two 22, 60,
+// 308, 1150.
 void group_levels(DevField& d) {
   const int64_t entry = d.f16 ? 4 : 8;
   int n = 0, nq = 0;
   for (int kind = 0; kind < 2; ++kind) {  // 0: hashed, 1: dense
     int64_t bytes = 0;
-    bool open = false;
+    int count = 0;  // levels of the open queue
     for (int l = 0; l < d.L; ++l) {
       if ((int)d.dense[l] != kind) continue;
       const int64_t v = kind ? (int64_t)d.n1[l] * d.n1[l] * d.n1[l] : (int64_t)d.T;
-      if (!open || bytes + v * entry > (kind ? kDenseGroupBytes : kGroupBytes)) {
+      const int64_t with = bytes + v * entry;
+      if (count == 0 || with > (kind ? kDenseGroupBytes : kGroupBytes) ||
+          (kind == 0 && count >= 2 && with > kSmallGroupBytes)) {
         d.q_first[nq++] = n;
         bytes = 0;
-        open = true;
+        count = 0;
       }
       bytes += v * entry;
+      ++count;
       d.q_level[n++] = l;
     }
     if (kind == 0) d.n_hashed_queue = nq;

@@ -23,9 +23,11 @@ constexpr int64_t kDeviceSizedBytes = (int64_t)16 << 30;  // worst-case sample b
                                                            // gradient may allocate to skip the
                                                            // host's read of the sample totals
 constexpr int kReduceParts = 64;      // parts per hypothesis of the reduction (lanes of one wave)
-// Level tables one encoding work queue may span: an XCD's L2 of hashed ones,
-// half of it of dense ones (see group_levels).
-constexpr int64_t kGroupBytes = (int64_t)4 << 20, kDenseGroupBytes = (int64_t)2 << 20;
+// Level tables one encoding work queue may span: two hashed ones within an XCD's
+// L2, more within four times a CU's L1, dense ones within half an XCD's L2 (see
+// group_levels).
+constexpr int64_t kGroupBytes = (int64_t)4 << 20, kDenseGroupBytes = (int64_t)2 << 20,
+                  kSmallGroupBytes = (int64_t)128 << 10;
 constexpr int kAdamState = 16;        // Adam state floats per hypothesis: m[6], v[6], n, 3 pads
 
 // A operand of one (row tile, K step) of v_mfma_f32_16x16x32_bf16: 8 bf16

@@ -160,3 +160,30 @@ def test_a_batch_takes_as_few_chunks_as_with_smaller_rays(lib):
     assert f.loss_grad(K=K, P=P, samples=samples) == pnerf.OK
     assert lib.fake_encodes() == 1
     f.close()
+
+
+@pytest.mark.parametrize("param_dtype", ["f32", "f16"])
+@pytest.mark.parametrize("n_levels", [4, 8, 12, 16])
+@pytest.mark.parametrize("log2_table", [4, 10, 11, 12, 13, 15, 17, 19, 20])
+def test_encoding_queues(lib, log2_table, n_levels, param_dtype):
+    # every level in one queue, hashed ones first and in order; a hashed queue of
+    # more than one level within an XCD's L2 (4 MiB), of more than two within 128 KiB
+    f = HostField(lib, log2_table=log2_table, n_levels=n_levels, param_dtype=param_dtype)
+    assert f.loss_grad(K=1, P=64, samples=100) == pnerf.OK
+    first, level, n_hashed = (C.c_int * 17)(), (C.c_int * 16)(), C.c_int()
+    n = lib.fake_queues(first, level, C.byref(n_hashed))
+    queues = [list(level[first[q]:first[q + 1]]) for q in range(n)]
+    T, entry = 1 << log2_table, 8 if param_dtype == "f32" else 4
+    n1 = [int(r) + 1 for r in synth.level_resolutions(n_levels, 16, 2048)]
+    hashed = [l for l in range(n_levels) if n1[l] ** 3 > T]
+    dense = [l for l in range(n_levels) if n1[l] ** 3 <= T]
+    assert sum(queues, []) == hashed + dense and all(queues)
+    for q, group in enumerate(queues):
+        assert all((l in hashed) == (q < n_hashed.value) for l in group)
+        size = sum(T if l in hashed else n1[l] ** 3 for l in group) * entry
+        if q >= n_hashed.value:
+            assert len(group) == 1 or size <= 2 << 20
+        else:
+            assert len(group) == 1 or size <= 4 << 20
+            assert len(group) <= 2 or size <= 128 << 10
+    f.close()
