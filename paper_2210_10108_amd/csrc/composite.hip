@@ -15,6 +15,7 @@ namespace pnerf {
 namespace {
 
 constexpr int kBlock = 256;
+constexpr int kReduceFewHyp = 8;  // two blocks per CU: loads are waited for, not covered
 
 template <int WITH_GRAD>
 __global__ __launch_bounds__(kBlock) void k_composite(DevField f, DevBatch b, DevWork w,
@@ -150,35 +151,58 @@ __device__ __forceinline__ void sample_terms(const DevField& f, const DevWork& w
 // Per-hypothesis reduction in two fixed-order stages.  Block (j, k) sums part
 // j of hypothesis k's rays (losses) and samples (torque and force terms): the
 // ranges are cut into n_parts equal pieces, each summed by a strided loop, a
-// wavefront scan and the four wavefronts' totals in order.  k_reduce_final adds the n_parts partials of each hypothesis in
-// order.  Same inputs give the same bits.
+// wavefront scan and the four wavefronts' totals in order.  k_reduce_final adds
+// the n_parts partials of each hypothesis in order.  Same inputs give the same
+// bits.
+//
+// WAVE: parts of at most 64 rays and samples, which only the first wavefront of
+// their block would have something of: each wavefront takes a part of its own.
+// Blocks of one part each are bound by their number (4.2 M of them: 3.97 ms for
+// 65535 hypotheses of 4 pixels, 0.94 with a part per wavefront; 1085 and 318 us
+// for 16384 of 16 pixels, 25.5 and 12.6 for 256 of 64).
+//
+// AHEAD: terms that a thread loads before it adds them, in the loop's order.  A
+// term waits for the sample's ray and then for that ray's record, which few
+// blocks do not cover: one hypothesis (64 blocks) of 1.6 M samples takes 51 us
+// with 4 and 71 with 1, four of 85 k samples 11.9 and 13.8; 16 of 27 k take 10.0
+// with 1 and 10.8 with 4.
+template <bool WAVE, int AHEAD>
 __global__ __launch_bounds__(kBlock) void k_reduce_partial(DevField f, DevBatch b, DevWork w,
                                                            int n_parts, float* partial) {
+  constexpr int kStride = WAVE ? 64 : kBlock;
   __shared__ float red[7][kBlock / 64];
-  int j = blockIdx.x, k = blockIdx.y, tid = threadIdx.x;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int j = WAVE ? blockIdx.x * (kBlock / 64) + wv : blockIdx.x, k = blockIdx.y;
+  const int tid = WAVE ? lane : threadIdx.x;
   int r0 = k * b.P, nr = b.P;
   int s0 = w.off[r0], ns = w.off[r0 + nr] - s0;
   int ra = r0 + (int)((int64_t)nr * j / n_parts), rb = r0 + (int)((int64_t)nr * (j + 1) / n_parts);
   int sa = s0 + (int)((int64_t)ns * j / n_parts), sb = s0 + (int)((int64_t)ns * (j + 1) / n_parts);
   float acc[7] = {0, 0, 0, 0, 0, 0, 0};
-  for (int r = ra + tid; r < rb; r += kBlock) acc[6] += w.ray_loss[r];
-  for (int s = sa + tid; s < sb; s += kBlock) {
-    float o[6];
-    sample_terms(f, w, s, o);
+  for (int r = ra + tid; r < rb; r += kStride) acc[6] += w.ray_loss[r];
+  for (int s = sa + tid; s < sb; s += AHEAD * kStride) {
+    float o[AHEAD][6];
 #pragma unroll
-    for (int q = 0; q < 6; ++q) acc[q] += o[q];
+    for (int u = 0; u < AHEAD; ++u) sample_terms(f, w, min(s + u * kStride, sb - 1), o[u]);
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+      if (s + u * kStride < sb)
+#pragma unroll
+        for (int q = 0; q < 6; ++q) acc[q] += o[u][q];
   }
-  const int lane = tid & 63, wv = tid >> 6;
+  float* const out = partial + ((size_t)k * n_parts + j) * 7;
 #pragma unroll
   for (int q = 0; q < 7; ++q) {
     const float v = wave_incl_scan(acc[q]);
-    if (lane == 63) red[q][wv] = v;
+    if (WAVE && lane == 63) out[q] = 0.0f + v;  // + 0: as the sum over wavefronts below
+    if (!WAVE && lane == 63) red[q][wv] = v;
   }
+  if (WAVE) return;
   __syncthreads();
   if (tid < 7) {
     float v = 0.0f;
     for (int u = 0; u < kBlock / 64; ++u) v += red[tid][u];
-    partial[((size_t)k * n_parts + j) * 7 + tid] = v;
+    out[tid] = v;
   }
 }
 
@@ -282,8 +306,17 @@ int reduce_parts(int K) {
 hipError_t launch_reduce(const DevField& f, const DevBatch& b, const DevWork& w, float* loss,
                          float* dpose, hipStream_t s) {
   int n_parts = reduce_parts(b.K);
-  hipLaunchKernelGGL(k_reduce_partial, dim3(n_parts, b.K), dim3(kBlock), 0, s, f, b, w, n_parts,
-                     w.partial);
+  const int64_t most = std::max<int64_t>(b.P, (int64_t)b.P * f.max_per_ray);  // samples
+  const int64_t longest = (most + n_parts - 1) / n_parts;                     // of one part
+  if (longest <= 64 && n_parts % (kBlock / 64) == 0)
+    hipLaunchKernelGGL((k_reduce_partial<true, 1>), dim3(n_parts / (kBlock / 64), b.K),
+                       dim3(kBlock), 0, s, f, b, w, n_parts, w.partial);
+  else if (b.K <= kReduceFewHyp)
+    hipLaunchKernelGGL((k_reduce_partial<false, 4>), dim3(n_parts, b.K), dim3(kBlock), 0, s, f, b,
+                       w, n_parts, w.partial);
+  else
+    hipLaunchKernelGGL((k_reduce_partial<false, 1>), dim3(n_parts, b.K), dim3(kBlock), 0, s, f, b,
+                       w, n_parts, w.partial);
   hipLaunchKernelGGL(k_reduce_final, dim3(b.K), dim3(64), 0, s, b.K, n_parts, w.partial, loss,
                      dpose);
   return hipGetLastError();

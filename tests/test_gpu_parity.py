@@ -291,6 +291,33 @@ def test_inspect_needs_a_backward_that_keeps_samples(pn):
     f.close()
 
 
+@pytest.mark.parametrize("sh_dir_grad", [0, 1])
+@pytest.mark.parametrize("K,P", [(1, 6000), (8, 700), (9, 700), (3, 128), (3, 130), (300, 3), (70, 1)])
+def test_gradient_is_the_sum_of_the_samples(pn, K, P, sh_dir_grad):
+    # the reduction's variants (parts of a wavefront up to 128 pixels of 32
+    # samples, terms loaded ahead up to 8 hypotheses), with parts without samples
+    # and the last terms of a part; sums of up to about 90 additions in a row
+    # (loop, scan, partials), each within 2^-24 of a partial sum
+    case = G.make_case("tiny32", K=K, P=P, sh_dir_grad=sh_dir_grad)
+    obs = G.to_dev(np.random.default_rng(0).uniform(0, 1, (32, 32, 3)).astype(np.float32))
+    poses, pix = G.to_dev(case.poses), G.to_dev(case.pix)
+    f = pn.Field(case.spec)
+    loss, dpose = (x.cpu().numpy() for x in f.render_loss_grad(poses, pix, obs, case.intr))
+    n = f.last_sample_count()
+    rows = f.inspect(3, n).cpu().numpy().astype(np.float64)
+    off, _, _ = f.march(poses, pix, case.intr, 0)
+    cut = off.cpu().numpy()[::P]
+    for k in range(K):
+        part = rows[cut[k]:cut[k + 1]]
+        assert np.all(np.abs(dpose[k] - part.sum(0)) <= 1e-5 * np.abs(part).sum(0) + 1e-30), k
+    # and the same bits whichever variant sums a hypothesis
+    for k in range(0, K, 1 + K // 4):
+        one = f.render_loss_grad(poses[k:k + 1].contiguous(), pix[k:k + 1].contiguous(), obs, case.intr)
+        assert np.array_equal(one[0].cpu().numpy()[0], loss[k])
+        assert np.array_equal(one[1].cpu().numpy()[0], dpose[k]), k
+    f.close()
+
+
 def test_inspect_after_a_refused_call(pn):
     # the refused call has marched its own rays: the samples of the call before
     # are still there, the rays that their torque is formed from are not
