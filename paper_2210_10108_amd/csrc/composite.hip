@@ -311,7 +311,7 @@ hipError_t launch_reduce(const DevField& f, const DevBatch& b, const DevWork& w,
   if (longest <= 64 && n_parts % (kBlock / 64) == 0)
     hipLaunchKernelGGL((k_reduce_partial<true, 1>), dim3(n_parts / (kBlock / 64), b.K),
                        dim3(kBlock), 0, s, f, b, w, n_parts, w.partial);
-  else if (b.K <= kReduceFewHyp)
+  else if (b.K <= kReduceFewHyp && longest >= 4 * kBlock)  // (a thread has 4 terms)
     hipLaunchKernelGGL((k_reduce_partial<false, 4>), dim3(n_parts, b.K), dim3(kBlock), 0, s, f, b,
                        w, n_parts, w.partial);
   else
