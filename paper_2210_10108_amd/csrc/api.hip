@@ -717,7 +717,7 @@ pnerf_status run(pnerf_field* F, Mode mode, int32_t K, const float* poses, int32
                                       sums[c], s));
       } else if (mode == kRender) {
         HIP_TRY(timed(F, "encode_render", s, [&] {
-          return launch_encode(F->dev, b, w, sums[c], F->enc_blocks, F->n_cu, 0, s);
+          return launch_encode(F->dev, w, sums[c], F->enc_blocks, F->n_cu, 0, s);
         }));
         HIP_TRY(timed(F, "mlp_fwd_render", s, [&] {
           return launch_mlp_fwd(F->dev, b, w, F->fwd_blocks, 0, s);
@@ -728,7 +728,7 @@ pnerf_status run(pnerf_field* F, Mode mode, int32_t K, const float* poses, int32
       } else {
         const int eb = overlap ? F->enc_blocks_overlap : F->enc_blocks;
         HIP_TRY(timed(F, "encode", se, [&] {
-          return launch_encode(F->dev, b, w, sums[c] >= 0 ? sums[c] : worst, eb, F->n_cu, 1, se);
+          return launch_encode(F->dev, w, sums[c] >= 0 ? sums[c] : worst, eb, F->n_cu, 1, se);
         }));
         if (overlap) {
           HIP_TRY(hipEventRecord(F->ev_enc[slot], se));

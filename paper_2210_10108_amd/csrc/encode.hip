@@ -582,12 +582,35 @@ __device__ __forceinline__ void dense_item(const DevField& f, const DevWork& w, 
   }
 }
 
+// Blocks that work on a batch: 4 per CU (kFewPerCu), and all 7 that are resident
+// from kManyItems items on.  More blocks cover the gathers' latency better, but
+// each finds the queues drained one by one at the end and holds lines of the L1.
+// Encode with 4 and with 7 per CU, us, at so many thousand items.  Uniform samples
+// of 16 levels: fp32, 2^19 entries: 38 294 308, 146 1182 1192, 391 3081 3053, 791
+// 6305 6255 (without gradient 146 1080 1089, 195 1419 1406, 391 2726 2707); fp32,
+// 2^21: 156 2696 2713, 416 6815 6816, 843 13935 13871; fp16, 2^19: 22 269 281, 83
+// 1021 1051, 446 5481 5535.  Of 8 levels, fp32, 2^19: 23 165 175, 176 1172 1174,
+// 234 1498 1494, 475 3129 3072.  Lattice samples, which lie closer together, of 16
+// levels: fp32, 2^19: 30 227 244, 81 541 553; fp32, 2^21: 157 2059 2096; fp16,
+// 2^19: 23 254 264, 378 4000 3970; a whole call of 5.6 M samples (165) 1880 1859.
+constexpr int kFewPerCu = 4, kManyItems = 128 << 10;
+__host__ __device__ inline int work_items(const DevField& f, uint32_t samples) {
+  // (a batch is below 2^31 samples: at most 2^27 items)
+  return (int)((samples + kItem - 1) / kItem) * f.n_hashed_queue +
+         (int)((samples + kDenseItem - 1) / kDenseItem) * (f.n_queue - f.n_hashed_queue);
+}
+
 template <bool F16, bool GRAD>
-__global__ __launch_bounds__(kBlock) void k_encode(DevField f, DevBatch b, DevWork w) {
+__global__ __launch_bounds__(kBlock) void k_encode(DevField f, DevWork w, int n_few) {
   __shared__ int s_q[2];
   __shared__ uint32_t s_item[2];
   __shared__ float4 s_rec[kBlock / 64][3 * kWaveRays];
-  const int S = *w.total;
+  const int S = __builtin_amdgcn_readfirstlane(*w.total);
+  // the grid is sized for what the batch may hold at most: where it holds less,
+  // the blocks past n_few take no item (the others need not wait for S to know)
+  int working = 1;
+  if ((int)blockIdx.x >= n_few)
+    working = __builtin_amdgcn_readfirstlane(work_items(f, S) >= kManyItems);
   const uint32_t n_hashed = (uint32_t)((S + kItem - 1) / kItem);
   const uint32_t n_dense = (uint32_t)((S + kDenseItem - 1) / kDenseItem);
   const int lane = threadIdx.x & 63;
@@ -598,12 +621,12 @@ __global__ __launch_bounds__(kBlock) void k_encode(DevField f, DevBatch b, DevWo
   uint32_t drained = 0;                                   // thread 0's copy
   int q = home;
   int buf = 0;
-  if (threadIdx.x == 0) s_item[0] = take_item(w.queue, q);
+  if (working && threadIdx.x == 0) s_item[0] = take_item(w.queue, q);
   __syncthreads();
   uint32_t item = __builtin_amdgcn_readfirstlane(s_item[0]);
   // control flow below is uniform over the block: item and q follow from the
   // same shared words for every thread
-  while (true) {
+  while (working) {
     const bool hashed = q < f.n_hashed_queue;
     const uint32_t n_items = hashed ? n_hashed : n_dense;
     if (item >= n_items) {  // queue q is drained
@@ -695,32 +718,21 @@ __global__ __launch_bounds__(kBlock) void k_occupancy(DevField f, uint32_t* bits
 
 }  // namespace
 
-// Blocks for a batch of up to max_samples samples: no more than its work items,
-// and 4 per CU where the resident blocks (n_blocks, 7 per CU) would take fewer
-// than 64 items each: what every block spends on finding the queues drained is
-// then a share of the kernel (800 k samples on 16 levels: 224 us with 4 blocks
-// per CU, 242 us with 7; 39 M samples: 8.10 ms and 7.90 ms).
-static int useful_blocks(const DevField& f, int64_t max_samples, int n_blocks, int n_cu) {
-  const int64_t items = (max_samples + kItem - 1) / kItem * f.n_hashed_queue +
-                        (max_samples + kDenseItem - 1) / kDenseItem * (f.n_queue - f.n_hashed_queue);
-  if (items < (int64_t)n_blocks * 64) n_blocks = std::min(n_blocks, 4 * n_cu);
-  return (int)std::max<int64_t>(1, std::min<int64_t>(n_blocks, items));
-}
-
-hipError_t launch_encode(const DevField& f, const DevBatch& b, const DevWork& w,
-                         int64_t max_samples, int n_blocks, int n_cu, int with_grad,
-                         hipStream_t s) {
-  n_blocks = useful_blocks(f, max_samples, n_blocks, n_cu);
+hipError_t launch_encode(const DevField& f, const DevWork& w, int64_t max_samples, int resident,
+                         int n_cu, int with_grad, hipStream_t s) {
+  const int items = work_items(f, (uint32_t)max_samples), n_few = kFewPerCu * n_cu;
+  const int most = items < kManyItems ? std::min(resident, n_few) : resident;
+  const dim3 grid(std::max(1, std::min(most, items)));
   if (f.f16) {
     if (with_grad)
-      hipLaunchKernelGGL((k_encode<true, true>), dim3(n_blocks), dim3(kBlock), 0, s, f, b, w);
+      hipLaunchKernelGGL((k_encode<true, true>), grid, dim3(kBlock), 0, s, f, w, n_few);
     else
-      hipLaunchKernelGGL((k_encode<true, false>), dim3(n_blocks), dim3(kBlock), 0, s, f, b, w);
+      hipLaunchKernelGGL((k_encode<true, false>), grid, dim3(kBlock), 0, s, f, w, n_few);
   } else {
     if (with_grad)
-      hipLaunchKernelGGL((k_encode<false, true>), dim3(n_blocks), dim3(kBlock), 0, s, f, b, w);
+      hipLaunchKernelGGL((k_encode<false, true>), grid, dim3(kBlock), 0, s, f, w, n_few);
     else
-      hipLaunchKernelGGL((k_encode<false, false>), dim3(n_blocks), dim3(kBlock), 0, s, f, b, w);
+      hipLaunchKernelGGL((k_encode<false, false>), grid, dim3(kBlock), 0, s, f, w, n_few);
   }
   return hipGetLastError();
 }

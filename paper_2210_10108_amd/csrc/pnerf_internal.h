@@ -217,10 +217,9 @@ hipError_t launch_march_count(const DevField& f, const DevBatch& b, const DevWor
 hipError_t launch_march_write(const DevField& f, const DevBatch& b, const DevWork& wb,
                               const DevWork& wc, int ray_base, int sample_base, int chunk_total,
                               int raw_blocks, int32_t* lattice_j_out, hipStream_t s);
-// max_samples: what the batch may hold at most (no more blocks than its work items)
-hipError_t launch_encode(const DevField& f, const DevBatch& b, const DevWork& w,
-                         int64_t max_samples, int n_blocks, int n_cu, int with_grad,
-                         hipStream_t s);
+// max_samples: what the batch may hold at most; resident: blocks that the chip holds
+hipError_t launch_encode(const DevField& f, const DevWork& w, int64_t max_samples, int resident,
+                         int n_cu, int with_grad, hipStream_t s);
 hipError_t launch_mlp_fwd(const DevField& f, const DevBatch& b, const DevWork& w, int n_blocks,
                           int with_grad, hipStream_t s);
 hipError_t launch_composite(const DevField& f, const DevBatch& b, const DevWork& w, int with_grad,

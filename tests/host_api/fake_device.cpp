@@ -118,8 +118,7 @@ hipError_t launch_inspect(const DevField&, const DevBatch&, const DevWork& w, in
   dst[1] = what == 3 && w.rrec ? w.rrec[0].x : -1.0f;
   return hipSuccess;
 }
-hipError_t launch_encode(const DevField& f, const DevBatch&, const DevWork&, int64_t, int, int, int,
-                         hipStream_t) {
+hipError_t launch_encode(const DevField& f, const DevWork&, int64_t, int, int, int, hipStream_t) {
   ++g_encodes;
   g_field = f;
   return hipSuccess;
