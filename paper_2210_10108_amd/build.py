@@ -20,17 +20,25 @@ SOURCES = ["api.hip", "march.hip", "encode.hip", "mlp.hip", "composite.hip", "po
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         # the encoding claims its next work item before it needs it: without this the
-         # compiler broadcasts the atomic's result, and waits for it, at once
-         "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
          "-fhip-fp32-correctly-rounded-divide-sqrt", "-fno-gpu-rdc", "-ffp-contract=on",
          "-Wall", "-Wno-unused-function", "-Wno-unused-variable", "-Wno-unknown-pragmas",
          "-I", os.path.join(HERE, "..", "include")]
 
+SOURCE_FLAGS = {
+    # the encoding claims its next work item before it needs it: without this the
+    # compiler broadcasts the atomic's result, and waits for it, at once
+    "encode.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],
+}
+
+
+def flags(src: str) -> list[str]:
+    """The compiler flags of one source."""
+    return FLAGS + SOURCE_FLAGS.get(src, [])
+
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, src.replace(".hip", ".o"))
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *flags(src), "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{r.stderr}")

@@ -24,7 +24,7 @@ BUDGET = {
 
 
 def remarks(src, tmp_path):
-    cmd = [build.HIPCC, *build.FLAGS, "-Rpass-analysis=kernel-resource-usage", "-c",
+    cmd = [build.HIPCC, *build.flags(src), "-Rpass-analysis=kernel-resource-usage", "-c",
            os.path.join(build.CSRC, src), "-o", str(tmp_path / "k.o")]
     r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stderr[-2000:]
@@ -101,7 +101,7 @@ def unpadded_mfma_reads_after_branches(asm):
 @pytest.mark.parametrize("src", ["mlp.hip", "encode.hip", "composite.hip", "march.hip", "pose.hip"])
 def test_no_mfma_result_read_unpadded_after_a_branch(src, tmp_path):
     out = tmp_path / "k.s"
-    cmd = [build.HIPCC, *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, src),
+    cmd = [build.HIPCC, *build.flags(src), "--cuda-device-only", "-S", os.path.join(build.CSRC, src),
            "-o", str(out)]
     r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stderr[-2000:]
