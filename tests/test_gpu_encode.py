@@ -44,6 +44,8 @@ FIELDS = {
     "all_dense": (8, 18, 48, "f32", 1),
     "large_dense": (4, 22, 150, "f32", 1),
     "smallest_table": (4, 4, 64, "f16", 0),
+    # the last level is dense and fills its table: 256^3 = 2^24 vertices
+    "largest_dense": (4, 24, 255, "f16", 1),
 }
 
 

@@ -16,6 +16,8 @@ BUDGET = {
     "encode.hip": {"k_encodeILb0ELb1E": 7},
     # <levels per lane group, (SH direction path,) (keep,) fp16>
     "mlp.hip": {"k_mlp_fwdILi4ELb1ELb0E": 8, "k_mlp_bwdILi4ELb0ELb0E": 7,
+                # 3 of the forward's 8-wavefront blocks per CU at 4, 8 and 12 levels
+                "k_mlp_fwd": 7,
                 "k_mlp_bwdILi4ELb1ELb0E": 6, "k_mlp_fwdILi4ELb1ELb1E": 8,
                 "k_mlp_bwdILi4ELb0ELb1E": 8, "k_mlp_bwdILi4ELb1ELb1E": 6,
                 # every variant of the fused backward: 2 of its 8-wavefront blocks per CU
