@@ -16,13 +16,15 @@
 // flips, the lowest bit for even x.  Each gather instruction so touches about
 // half as many lines as with one lane per sample, and the gather's cost follows
 // the lines: a line that misses the CU's L1 takes 2.25 cycles from L2 at best
-// (measured over 1 to 4 MB), and the L1 keeps only about 64 such misses in
-// flight.  Each lane blends its half; one lane-pair exchange completes the
-// sums.  Dense levels take one lane per sample (dense_item).
+// (measured over 1 to 4 MB).  Each lane blends its half; one lane-pair exchange
+// completes the sums.  Dense levels take one lane per sample (dense_item).
 //
-// What bounds it: 4 lines per sample and hashed level at the L1's misses in
-// flight times the L2's latency, then the texture unit (16 cycles for any
-// gather instruction, 32 for a 16-byte load) and the vector work beside it.  On
+// What bounds it: 4 lines per sample and hashed level, fetched from L2 with about
+// 65 of them in flight per CU (tables of 4 MiB; 83 with 16 MiB tables, whose lines
+// come from memory, so 65 is no cap of the L1), at half the rate above.  More
+// wavefronts do not raise it (4 and 7 blocks per CU are within 1 % of each other
+// on large batches).  Then the texture unit (16 cycles for any gather
+// instruction, 32 for a 16-byte load) and the vector work beside it.  On
 // 39.5 M samples (16 levels, 2^19 entries, fp32) the kernel takes 7.7 ms
 // against 8.6 ms with per-lane ray lookups, positions recovered in float and a
 // queue per dense level; with every gather in L1 it took 5.0 ms, without
@@ -221,20 +223,20 @@ struct Level {
   uint32_t mask;  // table entries - 1
 };
 
-// The four corners of a lane's half of a cell: byte offsets in the level's table
-// (bit 0 of the index: y + 1, bit 1: z + 1).
-//
-// Dense: one 24-bit multiply-add per axis (n1^2 < 2^16), and the four corners
-// are four scalar bases with one lane offset.  Hashed: bits below T <= 2^24 of
-// y p1 and z p2 follow from the factors' low 24 bits (y, z <= 2^20), so 24-bit
-// multiplies do; the second row is the first plus the prime, and everything is
-// kept shifted by the entry size.
+// Byte offset of a cell's lowest corner in a dense level's table: a 24-bit
+// multiply-add per axis (n1^3 <= T <= 2^24, so n1 <= 256 and z n1 + y < 2^16).
+// The other corners are the same offset from other scalar bases.
 template <bool F16>
-__device__ __forceinline__ uint32_t dense_offset(const Level& lv, const Cell& c, int side) {
+__device__ __forceinline__ uint32_t dense_offset(const Level& lv, const Cell& c) {
   const uint32_t n1 = lv.res + 1;
-  return (__umul24(__umul24(c.i0[2], n1) + c.i0[1], n1) + c.i0[0] + side) << (F16 ? 2 : 3);
+  return (__umul24(__umul24(c.i0[2], n1) + c.i0[1], n1) + c.i0[0]) << (F16 ? 2 : 3);
 }
 
+// Byte offsets of the four corners of a lane's half of a cell in a hashed level's
+// table (bit 0 of the index: y + 1, bit 1: z + 1).  Bits below T <= 2^24 of y p1
+// and z p2 follow from the factors' low 24 bits (y, z <= 2^20), so 24-bit
+// multiplies do; the second row is the first plus the prime, and everything is
+// kept shifted by the entry size.
 template <bool F16>
 __device__ __forceinline__ void hashed_offsets(const Level& lv, const Cell& c, int side,
                                                uint32_t off[4]) {
@@ -421,7 +423,7 @@ __device__ __forceinline__ Level level_of(const DevField& f, int l) {
   return lv;
 }
 
-// No derivative along a sample's clamped axes (record order: see finish).
+// No derivative along a sample's clamped axes (record order: see the top).
 __device__ __forceinline__ void clear_clamped(uint32_t r[3], uint32_t clamped) {
   const uint32_t keep = (clamped & 1u ? 0u : 0xFFFFu) | (clamped & 2u ? 0u : 0xFFFF0000u);
   r[0] &= keep;
@@ -538,7 +540,7 @@ __device__ __forceinline__ void dense_item(const DevField& f, const DevWork& w, 
     const Level lv = level_of(f, l);
     Cell c;
     make_cell(lv.res, ps.x, ps.dx, c);
-    const uint32_t off = dense_offset<F16>(lv, c, 0);
+    const uint32_t off = dense_offset<F16>(lv, c);
     const uint32_t n1 = lv.res + 1, r1 = n1 << (F16 ? 2 : 3), r2 = n1 * r1;
     float2 lo[4], hi[4];  // bit 0 of the index: y + 1, bit 1: z + 1
 #pragma unroll

@@ -36,8 +36,12 @@
 // and tile, 8 cycles each at 128 B a cycle for the CU's four SIMDs together:
 // 64% of the forward's time), the vector work (254 instructions per tile beside
 // 60 MFMA products, 50%) and the matrix pipe (48%), whose phases alternate
-// within a wavefront and overlap only across the 8 resident ones; the texture
-// unit takes 16 cycles for every load or store instruction.
+// within a wavefront and overlap only across the resident ones: 8 per SIMD of the
+// forward with gradient at 16 levels, 6 (65 to 67 registers) at 4, 8 and 12.
+// Holding those to 64 registers, and 8 wavefronts, by picking the output array
+// at the store made them no faster (5.4 M samples: 4 levels 310 us against 313, 8
+// levels 322 and 321, 12 levels 346 and 338).  The texture unit takes 16 cycles
+// for every load or store instruction.
 #include <algorithm>
 
 #include "pnerf_internal.h"

@@ -180,7 +180,7 @@ struct DevBatch {
 struct DevWork {
   // per ray (SoA, and one record)
   float4* rrec;                 // [n_rays][3] ray record: origin o and float unit direction d, then
-                                // the unit direction in double (ray_record)
+                                // the unit direction in double (RayRecord)
   float *rtn, *rtf, *rdelta;
   float* rsh;                   // [n_rays][16] SH basis of each ray's direction (sh16)
   int32_t* count;               // kept samples per ray
@@ -201,7 +201,7 @@ struct DevWork {
   float* feat;                  // [column tiles of 16][levels, by lane group][16][2] features (see
                                 // encode.hip); after the backward [6][cap]: force, dL/dd
   __half* jac;                  // [6L][cap] d feature / d pos: 12-byte records per sample and
-                                // level in 32-sample blocks (jac_record in encode.hip)
+                                // level in 32-sample blocks (see encode.hip)
   int64_t cap;                  // sample capacity (row stride of feat and jac)
   uint32_t* queue;              // [(kMaxLevels + 1) * kQueueStride] encoding work-queue counters
                                 // (word q * kQueueStride: items of queue q taken) and, last, the
