@@ -276,7 +276,7 @@ __device__ __forceinline__ void sample_dir(const DevWork& w, int s, float d[3]) 
 // Mask bits of a ReLU layer's 16 values t[m][i] of one column tile (unit
 // 16m + 4g + i): value v = 4m + i is K position v % 8 of K step v / 8, so its
 // bit is base + 4 (v / 8) + (v % 8) / 2, plus 16 for odd v (see relu_pack2).
-template <bool RAY>
+template <bool FREE>
 __device__ __forceinline__ void apply_mask(floatx4 (&t)[4], uint32_t mk, int base) {
 #pragma unroll
   for (int m = 0; m < 4; ++m)
@@ -284,7 +284,7 @@ __device__ __forceinline__ void apply_mask(floatx4 (&t)[4], uint32_t mk, int bas
     for (int i = 0; i < 4; ++i) {
       const int v = 4 * m + i;
       const int bit = base + 4 * (v / 8) + (v % 8) / 2 + 16 * (v & 1);
-      if (RAY) {  // the compiler's own choice of instructions (see bwd_tile)
+      if (FREE) {  // the compiler's own choice of instructions (see bwd_tile)
         if (!((mk >> bit) & 1u)) t[m][i] = 0.0f;
         continue;
       }
@@ -310,10 +310,10 @@ __device__ __forceinline__ void swap32(float x, float& lo, float& hi) {
 }
 
 // Sum of the four lane groups' values, in every group (as adding the values of
-// lanes l ^ 16, then l ^ 32).  RAY: see bwd_tile.
-template <bool RAY>
+// lanes l ^ 16, then l ^ 32).  FREE: see bwd_tile.
+template <bool FREE>
 __device__ __forceinline__ float group_sum(float x) {
-  if (RAY) {
+  if (FREE) {
     x += __shfl_xor(x, 16);
     return x + __shfl_xor(x, 32);
   }
@@ -541,6 +541,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // took 130 to 138, and one block per CU).  k_ray_bwd on 5.4 M samples of 16
 // levels, with and without the three: 611 and 685 us, on the direction path 680
 // and 997, fp16 networks 510 and 611, on the direction path 567 and 657.
+//
+// The direction path of the separate kernel, at 6 wavefronts per SIMD, takes its
+// masks and sums that way too (not its records): 5.4 M samples of 16, 12, 8 and 4
+// levels 439, 397, 367 and 354 us against 449, 403, 374 and 358; fp16 networks 364,
+// 338, 311 and 282 against 368, 348, 322 and 289.
 template <int LPG, bool DIR, bool H, bool RAY = false>
 __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
                                          const typename Arith<H>::Unit* lds, const float (*s_c3)[16][3],
@@ -551,6 +556,7 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
   using A = Arith<H>;
   using Op = typename A::Op;
   constexpr int MD = (LPG + 1) / 2;  // row tiles of d loss / d feature
+  constexpr bool kFree = RAY || DIR;
   const int g = lane >> 4;
   const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
   // this lane group's Jacobian records of the sample (level 4j + g at record j),
@@ -589,7 +595,7 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
       const float* c3 = s_c3[g][4 * m + i];
       gb2[m][i] = c3[0] * z[0] + c3[1] * z[1] + c3[2] * z[2];
     }
-  apply_mask<RAY>(gb2, mw1, 0);
+  apply_mask<kFree>(gb2, mw1, 0);
   // colour layer 2 transposed
   floatx4 gb1[4] = {zero, zero, zero, zero};
 #pragma unroll
@@ -600,7 +606,7 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
 #pragma unroll
     for (int m = 0; m < 4; ++m) gb1[m] = A::mma(A::load(lds, kBC2 + 2 * m + s2, lane), x, gb1[m]);
   }
-  apply_mask<RAY>(gb1, mw0, 8);
+  apply_mask<kFree>(gb1, mw0, 8);
   // colour layer 1 transposed: rows = h index (row 0 has zero weights); SH rows
   floatx4 gh = zero, gsh = zero;
 #pragma unroll
@@ -620,7 +626,7 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
 #pragma unroll
     for (int m = 0; m < 4; ++m) ga[m] = A::mma(A::load(lds, kBD2 + m, lane), x, zero);
   }
-  apply_mask<RAY>(ga, mw0, 0);
+  apply_mask<kFree>(ga, mw0, 0);
   // density layer 1 transposed: row 4g + i of tile mm = feature i % 2 of
   // level 4 (2 mm + i / 2) + g, so lane group g gets its own levels
   floatx4 gf[MD];
@@ -669,8 +675,8 @@ __device__ __forceinline__ void bwd_tile(const DevField& f, const DevWork& w,
   }
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    gx[a] = group_sum<RAY>(gx[a]) * (f.inv_ext[a] * unscale);  // d pos / d p = N_l / extent (N_l applied above)
-    if (DIR) gd[a] = group_sum<RAY>(gd[a]) * unscale;
+    gx[a] = group_sum<kFree>(gx[a]) * (f.inv_ext[a] * unscale);  // d pos / d p = N_l / extent (N_l applied above)
+    if (DIR) gd[a] = group_sum<kFree>(gd[a]) * unscale;
   }
 }
 
