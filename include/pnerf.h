@@ -147,7 +147,7 @@ typedef struct {
                                    0 = separate kernels: composite and loss,
                                    network backward per 16-sample tile, then
                                    the per-hypothesis reduction (default; the
-                                   faster on the measured workloads);
+                                   faster but on launch-bound batches);
                                    1 = one fused kernel, a wavefront per ray:
                                    composite, loss, composite backward, both
                                    networks' backward and the encoding's
